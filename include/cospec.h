@@ -431,6 +431,23 @@ cospec_status cospec_hybrid_attention(const void *q, const void *k, const void *
                                       int32_t Hkv, int32_t D, int32_t K, float scale, void *out,
                                       hipStream_t stream);
 
+/*
+ * cospec_hybrid_attention with scratch memory, for calls whose query groups (one per
+ * sequence and key/value head) are too few to fill the GPU: their keys are then cut into
+ * pieces that run side by side, and a second kernel merges each query's pieces.
+ * cospec_hybrid_attention_workspace_size gives the bytes (0: the call is not cut, or the
+ * sizes are invalid).  workspace NULL: not cut, the same as cospec_hybrid_attention;
+ * otherwise 256-byte aligned and at least that large, else COSPEC_ERR_WORKSPACE.  The
+ * pieces' sums are fp32; the result differs from the uncut one by rounding only.
+ */
+size_t cospec_hybrid_attention_workspace_size(int32_t B, int32_t n_q, int32_t L, int32_t Hq, int32_t Hkv,
+                                              int32_t D);
+
+cospec_status cospec_hybrid_attention_ws(const void *q, const void *k, const void *v, const int32_t *ctx_len,
+                                         const int32_t *q_start, int32_t B, int32_t n_q, int32_t L, int32_t Hq,
+                                         int32_t Hkv, int32_t D, int32_t K, float scale, void *out,
+                                         void *workspace, size_t workspace_bytes, hipStream_t stream);
+
 /* Workspace bytes cospec_arbitrate needs (0 for invalid sizes). */
 size_t cospec_arbitrate_workspace_size(int64_t n_sel, const cospec_head *head);
 

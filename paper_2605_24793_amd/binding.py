@@ -125,6 +125,11 @@ def lib():
         L.cospec_hybrid_attention.restype = I32
         L.cospec_hybrid_attention.argtypes = [P, P, P, P, P, I32, I32, I32, I32, I32, I32, I32,
                                               ctypes.c_float, P, P]
+        L.cospec_hybrid_attention_workspace_size.restype = SZ
+        L.cospec_hybrid_attention_workspace_size.argtypes = [I32] * 6
+        L.cospec_hybrid_attention_ws.restype = I32
+        L.cospec_hybrid_attention_ws.argtypes = [P, P, P, P, P, I32, I32, I32, I32, I32, I32, I32,
+                                                 ctypes.c_float, P, P, SZ, P]
         L.cospec_arbitrate.restype = I32
         L.cospec_arbitrate.argtypes = [P, I64, P, I64, HP, ctypes.c_float, P, P, P, SZ, P]
         _lib = L
@@ -581,7 +586,10 @@ def hybrid_attention(q, k, v, ctx_len, q_start, K: int, scale: float) -> torch.T
     ctx = _i32(ctx_len, B, "ctx_len")
     qs = _i32(q_start, B, "q_start")
     out = torch.empty_like(q)
-    code = lib().cospec_hybrid_attention(_ptr(q), _ptr(k), _ptr(v), _ptr(ctx), _ptr(qs), B, nq, L, Hq, Hkv,
-                                         D, int(K), float(scale), _ptr(out), _stream())
+    lb = lib()
+    ws_bytes = lb.cospec_hybrid_attention_workspace_size(B, nq, L, Hq, Hkv, D)
+    ws = torch.empty(ws_bytes, dtype=torch.uint8, device=q.device) if ws_bytes else None
+    code = lb.cospec_hybrid_attention_ws(_ptr(q), _ptr(k), _ptr(v), _ptr(ctx), _ptr(qs), B, nq, L, Hq, Hkv,
+                                         D, int(K), float(scale), _ptr(out), _ptr(ws), ws_bytes, _stream())
     _check(code, "cospec_hybrid_attention")
     return out

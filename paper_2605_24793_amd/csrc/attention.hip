@@ -29,6 +29,12 @@
 // and O^T += V^T P^T takes its A operand (V^T) from the row-major V tile with the
 // gfx950 transposing LDS read (ds_read_b64_tr_b16), leaving O^T[d][query] in the
 // lane that owns the query, so rescaling needs no exchange.
+//
+// Few groups (small batches) leave most CUs without work, so their keys are cut into
+// pieces (attn_plan): the SPLIT form writes each piece's unnormalised sums, and
+// k_attention_combine merges them.  Two sequences of 16401 and 8209 positions, 8 key/value
+// heads, 17 queries of 32 heads: 330 us on 16 workgroups, 32 us in pieces of 1056 keys
+// (25 us of it the pieces, 4.5 us the merge; 101 MB of keys and values).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -109,6 +115,10 @@ template <int N> __device__ inline void lds_wait(u32x2 (&x)[N], u32x2 (&y)[N]) {
     for (int i = 0; i < N; ++i) asm volatile("" : "+v"(x[i]), "+v"(y[i]));
 }
 
+// A value that is the same in every lane, for the scalar registers (a buffer descriptor
+// built from a value the compiler keeps in a vector register costs a loop per load).
+__device__ inline int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
 // XOR swizzles of the LDS tiles (rows of RB = 2D bytes).  K: 16-byte units, so that
 // 16 consecutive rows read at one column hit distinct banks; V: 32-byte units, so
 // that the 8 rows of a transposing read do.
@@ -163,7 +173,10 @@ __global__ __launch_bounds__(256) void k_hybrid_mask(MaskArgs a) {
     }
 }
 
-template <int D>
+// SPLIT: the keys of every group are cut into pieces of a.chunk rows (a multiple of
+// kKeyBlock), one workgroup each, and the workgroup leaves its rows' unnormalised sums,
+// running max and weight sum in the workspace for k_attention_combine.
+template <int D, bool SPLIT>
 __global__ __launch_bounds__(64 * kMaxWaves) void k_hybrid_attention(AttnArgs a) {
     constexpr int RB = D * 2;                               // bytes per key/value row
     constexpr int SB = kKeyBlock * RB;                      // bytes of one tile per stage
@@ -174,41 +187,51 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_hybrid_attention(AttnArgs a)
     __shared__ __attribute__((aligned(16))) char s_k[kStages][SB];
     __shared__ __attribute__((aligned(16))) char s_v[kStages][SB];
 
-    const int grp = a.Hq / a.Hkv;
+    const int grp = a.by_grp.d;
     const int rows = a.n_q * grp;                           // query rows of one (sequence, kv head)
-    const int nthr = blockDim.x, wg_rows = nthr / 4;       // 16 rows per wave
-    const int wgs_per = (rows + wg_rows - 1) / wg_rows;
-    const int b = blockIdx.x / (a.Hkv * wgs_per);
-    const int h = (blockIdx.x / wgs_per) % a.Hkv;
-    const int q0 = (blockIdx.x % wgs_per) * wg_rows;
+    const int wg_rows = blockDim.x / 4;                     // 16 rows per wave
+    const uint32_t unit = SPLIT ? quot(a.by_splits, blockIdx.x) : blockIdx.x;
+    const int split = SPLIT ? blockIdx.x - unit * a.splits : 0;
+    const uint32_t bh = quot(a.by_wgs, unit);
+    const int b = quot(a.by_hkv, bh);
+    const int h = bh - b * a.Hkv;
+    const int q0 = (unit - bh * a.by_wgs.d) * wg_rows;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int g = lane >> 4, l16 = lane & 15;
 
-    const int lc = max(a.ctx_len[b], 0);
-    const int ln = static_cast<int>(min(static_cast<int64_t>(lc) + 2 * a.K + 3, static_cast<int64_t>(a.L)));
-    const int qs = a.q_start[b];
-    // the last key any query of this workgroup sees
-    const int r_hi = min(q0 + wg_rows, rows) - 1;
-    const int p_hi = qs + r_hi / grp;
-    const int kend = p_hi >= lc ? ln : min(p_hi + 1, ln);
-
-    // this lane's query column
+    // this lane's query column; its loads wait for no other load
     const int qi = q0 + wave * 16 + l16;
     const bool qvalid = qi < rows;
-    const int r = qvalid ? qi / grp : 0;
-    const int hq = h * grp + (qvalid ? qi % grp : 0);
-    const int p = qs + r;
-    const bool live = qvalid && p >= 0 && p < ln;
-    const int vis = p < lc ? p + 1 : ln;                   // keys [0, vis) are visible
+    const int r = qvalid ? quot(a.by_grp, qi) : 0;
+    const int hq = h * grp + (qvalid ? qi - r * grp : 0);
     u32x4 qf[DS];
     const char *qrow = static_cast<const char *>(a.q) + ((static_cast<int64_t>(b) * a.n_q + r) * a.Hq + hq) * D * 2;
 #pragma unroll
-    for (int s = 0; s < DS; ++s)
-        qf[s] = live ? *reinterpret_cast<const u32x4 *>(qrow + (32 * s + 8 * g) * 2) : u32x4{0, 0, 0, 0};
+    for (int s = 0; s < DS; ++s) qf[s] = *reinterpret_cast<const u32x4 *>(qrow + (32 * s + 8 * g) * 2);
+
+    const int lc = uniform(max(a.ctx_len[b], 0));
+    const int ln = static_cast<int>(min(static_cast<int64_t>(lc) + 2 * a.K + 3, static_cast<int64_t>(a.L)));
+    const int qs = uniform(a.q_start[b]);
+    // the last key any query of this workgroup sees
+    const int r_hi = min(q0 + wg_rows, rows) - 1;
+    const int p_hi = qs + static_cast<int>(quot(a.by_grp, r_hi));
+    const int kvis = p_hi >= lc ? ln : min(p_hi + 1, ln);
+    // this workgroup's keys [kbeg, kend); a piece past the last visible key is left by
+    // the whole workgroup (the combine reads only pieces that hold a visible key)
+    const int kbeg = split * (SPLIT ? a.chunk : 0);
+    if (SPLIT && kbeg >= kvis) return;
+    const int kend = uniform(SPLIT ? min(kvis, kbeg + a.chunk) : kvis);
+
+    const int p = qs + r;
+    const bool live = qvalid && p >= 0 && p < ln;
+    const int vis = p < lc ? p + 1 : ln;                   // keys [0, vis) are visible
     // the query loads complete here, not at their first use inside the key loop (where
     // the wait would also cover every key/value load issued after them)
 #pragma unroll
-    for (int s = 0; s < DS; ++s) asm volatile("" : "+v"(qf[s]));
+    for (int s = 0; s < DS; ++s) {
+        asm volatile("" : "+v"(qf[s]));
+        qf[s] = live ? qf[s] : u32x4{0, 0, 0, 0};
+    }
 
     floatx4 o[DT];
 #pragma unroll
@@ -244,9 +267,9 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_hybrid_attention(AttnArgs a)
         koff[q] = lrow * row_b + (pch ^ swz_k<RB>(lrow)) * 16;
         voff[q] = lrow * row_b + (((pch >> 1) ^ swz_v<RB>(lrow)) * 2 + (pch & 1)) * 16;
     }
-    const int nblk = (kend + kKeyBlock - 1) / kKeyBlock;
+    const int nblk = (kend - kbeg + kKeyBlock - 1) / kKeyBlock;
     auto issue = [&](int j) {
-        const uint32_t off = static_cast<uint32_t>(j * kKeyBlock) * row_b;
+        const uint32_t off = static_cast<uint32_t>(kbeg + j * kKeyBlock) * row_b;
         const char *lk = s_k[j % kStages] + wave * LPW * 1024;
         const char *lv = s_v[j % kStages] + wave * LPW * 1024;
 #pragma unroll
@@ -268,7 +291,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_hybrid_attention(AttnArgs a)
         if (loader && j + kStages - 1 < nblk) issue(j + kStages - 1);
         const char *sk = s_k[j % kStages];
         const char *sv = s_v[j % kStages];
-        const int k0 = j * kKeyBlock;
+        const int k0 = kbeg + j * kKeyBlock;
 
         // S^T[key][query] for the block: tile c holds keys 16c + 4g + jj in element jj
         floatx4 st[2];
@@ -346,6 +369,16 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_hybrid_attention(AttnArgs a)
 
     l = sum_rows(l);
     if (!qvalid) return;
+    if constexpr (SPLIT) {
+        // nontemporal stores: read once, by the combine
+        const int64_t rows_all = static_cast<int64_t>(a.B) * a.n_q * a.Hq;
+        const int64_t R = split * rows_all + (static_cast<int64_t>(b) * a.n_q + r) * a.Hq + hq;
+        float *po = a.part_o + R * D + 4 * g;
+#pragma unroll
+        for (int t = 0; t < DT; ++t) __builtin_nontemporal_store(o[t], reinterpret_cast<floatx4 *>(po + 16 * t));
+        if (g == 0) a.part_ml[R] = make_float2(m, l);
+        return;
+    }
     // O^T tile t, element j: d = 16t + 4g + j of this lane's query
     char *orow = static_cast<char *>(a.out) + ((static_cast<int64_t>(b) * a.n_q + r) * a.Hq + hq) * D * 2;
     const float inv = live && l > 0.f ? 1.f / l : 0.f;
@@ -357,7 +390,109 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_hybrid_attention(AttnArgs a)
     }
 }
 
+// One wave per query row: merges the row's pieces.  The pieces that hold a key the row
+// sees are [0, ceil(vis / chunk)); lane s weighs piece s (at most 64), then D / 4 lanes
+// take one piece's four output columns each, 64 / (D / 4) pieces side by side.
+template <int D>
+__global__ __launch_bounds__(256) void k_attention_combine(AttnArgs a) {
+    constexpr int LP = D / 4;                              // lanes of one piece
+    constexpr int SP = 64 / LP;                            // pieces side by side
+    constexpr int U = 4;                                   // loads in flight per lane
+    const int lane = threadIdx.x & 63;
+    const int64_t rows_all = static_cast<int64_t>(a.B) * a.n_q * a.Hq;
+    const int64_t R = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+    if (R >= rows_all) return;                             // whole wave leaves
+    const int b = quot(a.by_seq_rows, static_cast<uint32_t>(R));
+    const int r = quot(a.by_hq, static_cast<uint32_t>(R)) - static_cast<uint32_t>(b) * a.n_q;
+    const int lc = max(a.ctx_len[b], 0);
+    const int ln = static_cast<int>(min(static_cast<int64_t>(lc) + 2 * a.K + 3, static_cast<int64_t>(a.L)));
+    const int p = a.q_start[b] + r;
+    const bool live = p >= 0 && p < ln;
+    const int vis = !live ? 0 : p < lc ? p + 1 : ln;
+    const int n = (vis + a.chunk - 1) / a.chunk;           // <= a.splits <= 64
+    float2 ml = make_float2(-INFINITY, 0.f);
+    if (lane < n) ml = a.part_ml[lane * rows_all + R];
+    float M = ml.x;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
+    const float w = ml.y > 0.f ? __builtin_amdgcn_exp2f(ml.x - M) : 0.f;
+    float l = w * ml.y;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) l += __shfl_xor(l, off);
+    const int c = lane % LP, sp = lane / LP;
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < n; s0 += SP * U) {
+        floatx4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int s = min(s0 + u * SP + sp, n - 1);    // unconditional: clamped
+            v[u] = __builtin_nontemporal_load(reinterpret_cast<const floatx4 *>(a.part_o + (s * rows_all + R) * D) + c);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int s = s0 + u * SP + sp;
+            const float ws = __shfl(w, s & 63);
+            const bool in = s < n;                         // a piece counted twice by the clamp adds nothing
+#pragma unroll
+            for (int k = 0; k < 4; ++k) acc[k] = in ? fmaf(ws, v[u][k], acc[k]) : acc[k];
+        }
+    }
+#pragma unroll
+    for (int off = LP; off < 64; off <<= 1)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc[k] += __shfl_xor(acc[k], off);
+    if (sp == 0) {
+        const float inv = l > 0.f ? 1.f / l : 0.f;
+        const u32x2 q{bf16_pair(acc[0] * inv, acc[1] * inv), bf16_pair(acc[2] * inv, acc[3] * inv)};
+        *reinterpret_cast<u32x2 *>(static_cast<char *>(a.out) + (R * D + 4 * c) * 2) = q;
+    }
+}
+
+// Waves of a workgroup of the 16-row kernel: as many as the group's rows need, at most
+// kMaxWaves, spread evenly; at least four, the loaders among them.
+int64_t attn_waves(int64_t rows) {
+    const int64_t per_max = 16 * kMaxWaves;
+    const int64_t nwg = (rows + per_max - 1) / per_max;
+    return std::max<int64_t>(4, (((rows + nwg - 1) / nwg) + 15) / 16);
+}
+
+constexpr int64_t kCus = 256;         // compute units of an MI355X
+constexpr int64_t kMinChunk = 128;    // keys of a piece, at least
+
 }  // namespace
+
+// How the keys of a call are cut: the cheapest count by a cost in microseconds whose terms
+// were measured on MI355X with 68 query rows per group.  A workgroup alone on its CU takes
+// t1 per key (D = 128: 256 groups x 2065 keys 47.7 us), one that shares it t2 (512 groups
+// 76 us), the merge's launch 3.5 us, and each piece's sums are written and read back at
+// about 3 TB/s.  The cost agrees with the measured times of 16 to 256 groups, cut 1 to 32
+// times, within 3 us: 16 groups x 16401 keys 330 us uncut, 32.0 in 256 workgroups, 34.0 in
+// 512; 64 x 4017 31.5 in 256, 36.1 in 512; 96 x 2517 36.9 in 192, 32.5 in 480; 160 x 4113
+// 87 uncut, 79 in 320, 65 in 480; 224 x 2017 46 uncut, 53 in 448.  More groups than CUs are
+// not cut: two of them already share a CU.
+AttnPlan attn_plan(int32_t B, int32_t n_q, int32_t L, int32_t Hq, int32_t Hkv, int32_t D) {
+    AttnPlan p{1, 0, 0};
+    const int64_t rows = static_cast<int64_t>(n_q) * (Hq / Hkv);
+    if (B <= 0 || rows <= 0) return p;
+    const int64_t waves = attn_waves(rows);
+    const int64_t wgs = static_cast<int64_t>(B) * Hkv * ((rows + 16 * waves - 1) / (16 * waves));
+    if (wgs > kCus) return p;
+    const double t1 = D == 128 ? 0.023 : 0.0185, t2 = D == 128 ? 0.037 : 0.022;
+    const double piece_us = static_cast<double>(std::min<int64_t>(rows, 16 * waves)) * D * 8 / 3e6;
+    double best = L * t1;
+    for (int64_t s = 2; s <= 64 && wgs * s <= 2 * kCus; ++s) {
+        const int64_t chunk = ((L + s - 1) / s + kKeyBlock - 1) / kKeyBlock * kKeyBlock;
+        if (chunk < kMinChunk) break;
+        const int64_t n = (L + chunk - 1) / chunk;
+        const double cost = chunk * (wgs * n <= kCus ? t1 : t2) + 3.5 + piece_us * static_cast<double>(wgs * n);
+        if (n < 2 || cost >= best) continue;
+        best = cost;
+        p.splits = static_cast<int32_t>(n);
+        p.chunk = static_cast<int32_t>(chunk);
+        p.rows = static_cast<int64_t>(B) * n_q * Hq;
+    }
+    return p;
+}
 
 hipError_t launch_hybrid_mask(const MaskArgs &a, hipStream_t s) {
     const int64_t rows = static_cast<int64_t>(a.B) * a.L;
@@ -366,17 +501,33 @@ hipError_t launch_hybrid_mask(const MaskArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_hybrid_attention(const AttnArgs &a, hipStream_t s) {
+hipError_t launch_hybrid_attention(AttnArgs a, hipStream_t s) {
     const int64_t rows = static_cast<int64_t>(a.n_q) * (a.Hq / a.Hkv);
-    // as many waves as the group's rows need, at most kMaxWaves, spread evenly
-    const int64_t per_max = 16 * kMaxWaves;
-    const int64_t nwg = (rows + per_max - 1) / per_max;
-    const int64_t waves = std::max<int64_t>(4, (((rows + nwg - 1) / nwg) + 15) / 16);   // >= 4: loaders
+    const int64_t waves = attn_waves(rows);
     const int64_t wgs = static_cast<int64_t>(a.B) * a.Hkv * ((rows + 16 * waves - 1) / (16 * waves));
     if (wgs == 0) return hipSuccess;
     const dim3 block(static_cast<unsigned>(64 * waves));
-    if (a.D == 128) hipLaunchKernelGGL(k_hybrid_attention<128>, dim3(static_cast<unsigned>(wgs)), block, 0, s, a);
-    else hipLaunchKernelGGL(k_hybrid_attention<64>, dim3(static_cast<unsigned>(wgs)), block, 0, s, a);
+    a.by_grp = fast_div(a.Hq / a.Hkv);
+    a.by_wgs = fast_div(static_cast<uint32_t>((rows + 16 * waves - 1) / (16 * waves)));
+    a.by_hkv = fast_div(a.Hkv);
+    a.by_splits = fast_div(a.splits);
+    a.by_seq_rows = fast_div(static_cast<uint32_t>(a.n_q) * static_cast<uint32_t>(a.Hq));
+    a.by_hq = fast_div(a.Hq);
+    if (a.splits > 1) {
+        const dim3 grid(static_cast<unsigned>(wgs * a.splits));
+        const dim3 cgrid(static_cast<unsigned>((static_cast<int64_t>(a.B) * a.n_q * a.Hq + 3) / 4));
+        if (a.D == 128) {
+            hipLaunchKernelGGL((k_hybrid_attention<128, true>), grid, block, 0, s, a);
+            hipLaunchKernelGGL(k_attention_combine<128>, cgrid, dim3(256), 0, s, a);
+        } else {
+            hipLaunchKernelGGL((k_hybrid_attention<64, true>), grid, block, 0, s, a);
+            hipLaunchKernelGGL(k_attention_combine<64>, cgrid, dim3(256), 0, s, a);
+        }
+        return hipGetLastError();
+    }
+    const dim3 grid(static_cast<unsigned>(wgs));
+    if (a.D == 128) hipLaunchKernelGGL((k_hybrid_attention<128, false>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_hybrid_attention<64, false>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 

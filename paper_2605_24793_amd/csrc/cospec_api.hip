@@ -752,21 +752,69 @@ cospec_status cospec_hybrid_mask(const int32_t *ctx_len, int32_t B, int32_t K, i
     return launch_hybrid_mask(a, stream) == hipSuccess ? COSPEC_OK : COSPEC_ERR_HIP;
 }
 
-cospec_status cospec_hybrid_attention(const void *q, const void *k, const void *v, const int32_t *ctx_len,
-                                      const int32_t *q_start, int32_t B, int32_t n_q, int32_t L, int32_t Hq,
-                                      int32_t Hkv, int32_t D, int32_t K, float scale, void *out,
-                                      hipStream_t stream) {
-    if (B < 0 || n_q < 0 || L < 0 || K < 0 || Hq < 1 || Hkv < 1 || Hq % Hkv != 0 || !isfinite(scale))
-        return COSPEC_ERR_INVALID_ARG;
+// Sizes a hybrid-attention call may have (device values aside).
+static cospec_status attention_sizes(int32_t B, int32_t n_q, int32_t L, int32_t Hq, int32_t Hkv, int32_t D,
+                                     int32_t K) {
+    if (B < 0 || n_q < 0 || L < 0 || K < 0 || Hq < 1 || Hkv < 1 || Hq % Hkv != 0) return COSPEC_ERR_INVALID_ARG;
     if (D != 64 && D != 128) return COSPEC_ERR_UNSUPPORTED;
+    return COSPEC_OK;
+}
+
+static bool attention_too_large(int32_t B, int32_t n_q, int32_t L, int32_t Hq, int32_t Hkv, int32_t D) {
+    const int64_t wgs = static_cast<int64_t>(B) * Hkv * ((static_cast<int64_t>(n_q) * (Hq / Hkv) + 15) / 16);
+    return wgs > UINT32_MAX || static_cast<int64_t>(L) * Hkv * D > INT32_MAX;
+}
+
+// The pieces' sums, then their {max, weight sum} pairs.
+static size_t attention_sums_bytes(const AttnPlan &p, int32_t D) {
+    return round_up(static_cast<size_t>(p.splits) * static_cast<size_t>(p.rows) * static_cast<size_t>(D) * 4);
+}
+
+static size_t attention_ws_bytes(const AttnPlan &p, int32_t D) {
+    if (p.splits < 2) return 0;
+    return attention_sums_bytes(p, D) + round_up(static_cast<size_t>(p.splits) * static_cast<size_t>(p.rows) * 8);
+}
+
+size_t cospec_hybrid_attention_workspace_size(int32_t B, int32_t n_q, int32_t L, int32_t Hq, int32_t Hkv, int32_t D) {
+    if (attention_sizes(B, n_q, L, Hq, Hkv, D, 0) != COSPEC_OK || attention_too_large(B, n_q, L, Hq, Hkv, D)) return 0;
+    return attention_ws_bytes(attn_plan(B, n_q, L, Hq, Hkv, D), D);
+}
+
+cospec_status cospec_hybrid_attention_ws(const void *q, const void *k, const void *v, const int32_t *ctx_len,
+                                         const int32_t *q_start, int32_t B, int32_t n_q, int32_t L, int32_t Hq,
+                                         int32_t Hkv, int32_t D, int32_t K, float scale, void *out, void *workspace,
+                                         size_t workspace_bytes, hipStream_t stream) {
+    if (!isfinite(scale)) return COSPEC_ERR_INVALID_ARG;
+    const cospec_status st = attention_sizes(B, n_q, L, Hq, Hkv, D, K);
+    if (st != COSPEC_OK) return st;
     if (static_cast<int64_t>(B) * n_q == 0) return COSPEC_OK;
     if (!q || !aligned(q, 16) || !k || !aligned(k, 16) || !v || !aligned(v, 16) || !out || !aligned(out, 16) ||
         !ctx_len || !aligned(ctx_len, 4) || !q_start || !aligned(q_start, 4))
         return COSPEC_ERR_INVALID_ARG;
-    const int64_t wgs = static_cast<int64_t>(B) * Hkv * ((static_cast<int64_t>(n_q) * (Hq / Hkv) + 15) / 16);
-    if (wgs > UINT32_MAX || static_cast<int64_t>(L) * Hkv * D > INT32_MAX) return COSPEC_ERR_UNSUPPORTED;
-    AttnArgs a{q, k, v, ctx_len, q_start, B, n_q, L, Hq, Hkv, D, K, scale, out};
+    if (attention_too_large(B, n_q, L, Hq, Hkv, D)) return COSPEC_ERR_UNSUPPORTED;
+    AttnArgs a{};
+    a.q = q; a.k = k; a.v = v; a.ctx_len = ctx_len; a.q_start = q_start;
+    a.B = B; a.n_q = n_q; a.L = L; a.Hq = Hq; a.Hkv = Hkv; a.D = D; a.K = K;
+    a.scale = scale; a.out = out; a.splits = 1;
+    if (workspace) {
+        const AttnPlan p = attn_plan(B, n_q, L, Hq, Hkv, D);
+        if (p.splits > 1) {
+            if (!aligned(workspace, kAlign) || workspace_bytes < attention_ws_bytes(p, D)) return COSPEC_ERR_WORKSPACE;
+            a.splits = p.splits;
+            a.chunk = p.chunk;
+            a.part_o = static_cast<float *>(workspace);
+            a.part_ml = reinterpret_cast<float2 *>(static_cast<char *>(workspace) + attention_sums_bytes(p, D));
+        }
+    }
     return launch_hybrid_attention(a, stream) == hipSuccess ? COSPEC_OK : COSPEC_ERR_HIP;
+}
+
+cospec_status cospec_hybrid_attention(const void *q, const void *k, const void *v, const int32_t *ctx_len,
+                                      const int32_t *q_start, int32_t B, int32_t n_q, int32_t L, int32_t Hq,
+                                      int32_t Hkv, int32_t D, int32_t K, float scale, void *out,
+                                      hipStream_t stream) {
+    return cospec_hybrid_attention_ws(q, k, v, ctx_len, q_start, B, n_q, L, Hq, Hkv, D, K, scale, out, nullptr, 0,
+                                      stream);
 }
 
 size_t cospec_arbitrate_workspace_size(int64_t n_sel, const cospec_head *head) {

@@ -226,12 +226,39 @@ struct MaskArgs {
     uint8_t *mask;             // [B][L][L]
 };
 
+// Division by a divisor the host knows: x / d = high 64 bits of x * (floor((2^64 - 1) / d)
+// + 1), exact for every 32-bit x and d; d = 1 (whose multiplier is 2^64) is kept as m = 0.
+struct FastDiv {
+    uint64_t m;
+    uint32_t d;
+};
+
+inline FastDiv fast_div(uint32_t d) { return FastDiv{d <= 1 ? 0 : UINT64_MAX / d + 1, d}; }
+
+__device__ inline uint32_t quot(const FastDiv &f, uint32_t x) {
+    return f.m ? static_cast<uint32_t>(__umul64hi(f.m, x)) : x;
+}
+
 struct AttnArgs {
     const void *q, *k, *v;     // q [B][n_q][Hq][D], k and v [B][L][Hkv][D], bf16
     const int32_t *ctx_len, *q_start;
     int32_t B, n_q, L, Hq, Hkv, D, K;
     float scale;
     void *out;                 // [B][n_q][Hq][D] bf16
+    // keys cut into `splits` > 1 pieces of `chunk` rows: unnormalised sums [splits][rows][D]
+    // and {running max, weight sum} [splits][rows], rows = B * n_q * Hq
+    int32_t splits, chunk;
+    float *part_o;
+    float2 *part_ml;
+    // set by the launch: divisions by the query heads per key/value head, the workgroups
+    // per (sequence, key/value head), the key/value heads, the splits and n_q * Hq, Hq
+    FastDiv by_grp, by_wgs, by_hkv, by_splits, by_seq_rows, by_hq;
+};
+
+// How the keys of a hybrid-attention call are cut (splits 1: not at all).
+struct AttnPlan {
+    int32_t splits, chunk;
+    int64_t rows;              // B * n_q * Hq when the keys are cut, else 0
 };
 
 struct ArbFinishArgs {
@@ -260,6 +287,7 @@ hipError_t launch_finish(Dtype dt, const FinishArgs &a, hipStream_t s);
 hipError_t launch_arb_finish(const ArbFinishArgs &a, hipStream_t s);
 hipError_t launch_sps(Dtype dt, const SpsArgs &a, hipStream_t s);   // finish, weights, pick
 hipError_t launch_hybrid_mask(const MaskArgs &a, hipStream_t s);
-hipError_t launch_hybrid_attention(const AttnArgs &a, hipStream_t s);
+AttnPlan attn_plan(int32_t B, int32_t n_q, int32_t L, int32_t Hq, int32_t Hkv, int32_t D);
+hipError_t launch_hybrid_attention(AttnArgs a, hipStream_t s);   // the divisions are set here
 
 }  // namespace cospec

@@ -219,6 +219,28 @@ def test_hybrid_attention_arguments():
     assert attn(n_q=0) == OK
 
 
+def test_hybrid_attention_workspace():
+    L = cs.lib()
+    size = L.cospec_hybrid_attention_workspace_size
+    # pieces' sums (fp32) and {max, weight sum} of every query row, at least two pieces
+    need = size(2, 17, 16401, 32, 8, 128)
+    rows = 2 * 17 * 32
+    assert need >= 2 * rows * (128 * 4 + 8) and need % 256 == 0
+    assert size(64, 17, 2065, 32, 8, 128) == 0     # more groups than CUs: not cut
+    assert size(2, 17, 100, 8, 2, 128) == 0        # too short to cut
+    assert size(0, 17, 4096, 8, 2, 128) == 0 and size(2, 0, 4096, 8, 2, 128) == 0
+    for bad in ((-1, 17, 100, 8, 2, 128), (2, 17, 100, 6, 4, 128), (2, 17, 100, 8, 2, 96)):
+        assert size(*bad) == 0
+
+    def attn(ws, wsb, q=FAKE, D=128):
+        return L.cospec_hybrid_attention_ws(q, FAKE, FAKE, FAKE, FAKE, 2, 17, 16401, 32, 8, D, 7, 0.1, FAKE, ws, wsb,
+                                            None)
+    assert attn(FAKE, need - 1) == WORKSPACE
+    assert attn(FAKE + 16, 1 << 30) == WORKSPACE
+    assert attn(FAKE, need, q=None) == INVALID
+    assert attn(FAKE, need, D=96) == UNSUPPORTED
+
+
 def _tree(L, **kw):
     a = dict(tgt=FAKE, drf=FAKE, dt=1, ld=151936, par=FAKE, toks=FAKE, hid=FAKE, head=_head(),
              lam=0.5, B=4, N=60, V=151936, alen=FAKE, otok=FAKE, path=None, ws=FAKE, wsb=1 << 30,

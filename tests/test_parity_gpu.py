@@ -992,3 +992,33 @@ def test_hybrid_attention_long_prefill_several_workgroups():
     ctx = [250, 120]
     L = 250 + 2 * K + 3 + 9
     _attn_case(2, L, 2, 2, 64, L, ctx, [0, 0], K, seed=21)
+
+
+@pytest.mark.parametrize("B,nq,Hq,Hkv,D,ctx,L,K", [
+    (1, 17, 8, 2, 128, [128 * 3 - 17], 384, 7),        # whole pieces exactly
+    (2, 11, 7, 1, 64, [1500, 130], 1530, 4),           # a sequence that ends inside the second piece
+    (2, 17, 4, 4, 128, [2047, 0], 2064, 7),            # no context at all beside a long one
+    (1, 40, 8, 2, 128, [600], 700, 20),                # queries past the input, two workgroups per group
+    (1, 9, 2, 2, 64, [5000], 5009, 3),                 # many pieces per row
+])
+def test_hybrid_attention_in_pieces(B, nq, Hq, Hkv, D, ctx, L, K):
+    # few groups, long contexts: the keys are cut into pieces and merged
+    assert cs.lib().cospec_hybrid_attention_workspace_size(B, nq, L, Hq, Hkv, D) > 0
+    _attn_case(B, nq, Hq, Hkv, D, L, ctx, ctx, K, seed=B + nq)
+
+
+def test_hybrid_attention_pieces_match_uncut():
+    # the entry point without scratch memory runs uncut; both round P and the output to bf16
+    B, nq, Hq, Hkv, D, L, K = 2, 17, 8, 2, 128, 1217, 7
+    g = torch.Generator().manual_seed(5)
+    q, k, v = (torch.randn(B, n, h, D, generator=g).to(torch.bfloat16).to(DEV) for n, h in
+               ((nq, Hq), (L, Hkv), (L, Hkv)))
+    ctx = torch.tensor([1200, 700], dtype=torch.int32, device=DEV)
+    out = torch.empty_like(q)
+    rc = cs.lib().cospec_hybrid_attention(q.data_ptr(), k.data_ptr(), v.data_ptr(), ctx.data_ptr(), ctx.data_ptr(),
+                                          B, nq, L, Hq, Hkv, D, K, 0.09, out.data_ptr(),
+                                          torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    cut = cs.hybrid_attention(q, k, v, ctx, ctx, K, 0.09)
+    # each side's weights are rounded to bf16 (2^-9), its result too: 4 * 2^-9 of max |v|
+    assert (out.float() - cut.float()).abs().max().item() <= 4 * 2.0 ** -9 * v.float().abs().max().item()
