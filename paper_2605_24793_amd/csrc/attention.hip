@@ -14,9 +14,10 @@
 // Per round only the region's 2K+3 queries are new: their keys and values are
 // the cached context plus the region itself.
 //
-// Work split: the query rows (position x head) that share one key/value head of
+// Work split (k_hybrid_attention; k_hybrid_attention_wide below takes groups of more than
+// 128 rows): the query rows (position x head) that share one key/value head of
 // one sequence go to one workgroup of up to 8 waves, 16 rows per wave, so each
-// key and value is read once per group (more rows: more workgroups).  Keys and
+// key and value is read once per group.  Keys and
 // values stream through a ring of kStages LDS stages of kKeyBlock rows, filled
 // straight from HBM by raw buffer loads into LDS (no register staging): the
 // buffers end after the group's last visible row, so the hardware range check
@@ -214,8 +215,9 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_hybrid_attention(AttnArgs a)
     const int qs = uniform(a.q_start[b]);
     // the last key any query of this workgroup sees
     const int r_hi = min(q0 + wg_rows, rows) - 1;
+    const int p_lo = qs + static_cast<int>(quot(a.by_grp, q0));
     const int p_hi = qs + static_cast<int>(quot(a.by_grp, r_hi));
-    const int kvis = p_hi >= lc ? ln : min(p_hi + 1, ln);
+    const int kvis = p_lo >= ln ? 0 : p_hi >= lc ? ln : min(p_hi + 1, ln);   // all padding: no key
     // this workgroup's keys [kbeg, kend); a piece past the last visible key is left by
     // the whole workgroup (the combine reads only pieces that hold a visible key)
     const int kbeg = split * (SPLIT ? a.chunk : 0);
@@ -390,6 +392,261 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_hybrid_attention(AttnArgs a)
     }
 }
 
+// ---------------------------------------------------------------- many query rows
+
+typedef __attribute__((ext_vector_type(16))) float floatx16;
+typedef __attribute__((ext_vector_type(4))) short shortx4;
+
+constexpr int kWideKeys = 64;         // keys per LDS stage
+constexpr int kWideWaves = 4;         // 32 query rows each
+constexpr int kWideRows = 32 * kWideWaves;
+
+__device__ inline floatx16 mfma32(u32x4 a, u32x4 b, floatx16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b),
+                                                   c, 0, 0, 0);
+}
+
+// 16 bytes per lane from a raw buffer into LDS at byte lds + 16 * lane, lds the same in every
+// lane (zeros past the buffer's end).  Written as assembly, so that the compiler, which knows nothing of these loads,
+// places no wait for them before the LDS reads; the kernel's own waits order them.  M0 is
+// declared clobbered and nothing else in the kernel uses it.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ inline void load_lds16_asm(u32x4 rsrc, uint32_t off, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 :
+                 : "s"(lds), "v"(off), "s"(rsrc)
+                 : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
+__device__ inline uint32_t lds_addr(const char *p) {
+    return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_cchar *)p));
+}
+
+__device__ inline u32x4 raw_rsrc(const char *p, int bytes) {
+    const uint64_t addr = reinterpret_cast<uint64_t>(p);
+    return u32x4{static_cast<uint32_t>(uniform(static_cast<int>(addr))),
+                 static_cast<uint32_t>(uniform(static_cast<int>(addr >> 32))) & 0xffffu,
+                 static_cast<uint32_t>(uniform(bytes)), static_cast<uint32_t>(kRawBuffer)};
+}
+
+// The transposing LDS read of the kernel above as the builtin: every load into LDS of this
+// kernel is assembly, so the compiler tracks the read like any other.
+__device__ inline u32x2 read_tr_tracked(const char *lds) {
+    typedef __attribute__((address_space(3))) shortx4 lds_shortx4;
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)(lds_cchar *)lds));
+}
+
+// XOR swizzle of the value tiles (32-byte units): 32 lanes of a transposing read take two
+// neighbouring units of each of four rows, so rows 0..3 (modulo 4) shift by pairs of units.
+template <int RB> __device__ inline int swz_vw(int row) { return RB == 256 ? 2 * (row & 3) : row & 2; }
+
+// The same attention for calls with many query rows per (sequence, key/value head), such as
+// a first pass over a whole input.  There the matrix cores and the LDS bound it: sixteen
+// rows per wave read every key and value from LDS twice as often as the products need.  So
+// a wave takes 32 rows (32 x 32 products, D / 32 output tiles in registers), four waves
+// share a two-stage ring of 64-key stages (64 KB), and two workgroups share a CU, so that
+// one's softmax runs beside the other's products.  Measured, 4 sequences of 1041 to 2065
+// positions, 32/8 heads, D = 128 (84 GFLOP): 200 us with 16-row waves (50 us of it on
+// tiles of padding rows, which now read no key), 109-115 us here = 750 TFLOP/s, the issued
+// products alone 42 us.  Also measured there: eight waves with four stages 116 us, 32-key
+// stages 114 to 122, the next block's scores taken beside this block's softmax 118, three
+// waves per SIMD spill.  Without the loads the same code takes 94 us, without the
+// exponentials 104.
+template <int D>
+__global__ __launch_bounds__(64 * kWideWaves, 2) void k_hybrid_attention_wide(AttnArgs a) {
+    constexpr int RB = D * 2;                               // bytes per key/value row
+    constexpr int SB = kWideKeys * RB;                      // bytes of one tile per stage
+    constexpr int LPW = SB / 1024 / kWideWaves;             // 1 KB load instructions per tile and wave
+    constexpr int DS = D / 16;                              // MFMA k-steps over d
+    constexpr int DT = D / 32;                              // d tiles of the output
+    constexpr int KT = kWideKeys / 32;                      // key tiles of a stage
+    __shared__ __attribute__((aligned(16))) char s_k[2][SB];   // two stages of keys
+    __shared__ __attribute__((aligned(16))) char s_v[2][SB];   // ... and of values
+
+    const int grp = a.by_grp.d;
+    const int rows = a.n_q * grp;
+    // Workgroups are dealt to the XCDs round-robin: with a multiple of kXcds groups
+    // (a.splits = kXcds, else 1) a group's workgroups stay on one XCD, whose L2 then holds
+    // its keys and values.  The last query rows come first: they see the most keys.  Group
+    // by group (a.chunk = 0, by_wgs the tiles of a group), so that few groups' keys share
+    // an L2 at a time; tile by tile over all groups (a.chunk = 1, by_wgs the groups of an
+    // XCD) when every workgroup is resident at once.
+    const bool dealt = a.splits > 1;
+    const uint32_t x = dealt ? blockIdx.x % kXcds : 0, i0 = dealt ? blockIdx.x / kXcds : blockIdx.x;
+    const uint32_t q0t = quot(a.by_wgs, i0), rem = i0 - q0t * a.by_wgs.d;
+    const uint32_t t0 = a.chunk ? q0t : rem, lg = a.chunk ? rem : q0t;
+    const uint32_t bh = lg * (dealt ? kXcds : 1) + x;
+    const int b = quot(a.by_hkv, bh);
+    const int h = bh - b * a.Hkv;
+    const int tiles = (rows + kWideRows - 1) / kWideRows;
+    const int q0 = (tiles - 1 - static_cast<int>(t0)) * kWideRows;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int g = lane >> 5, l32 = lane & 31, l16 = lane & 15, dh = (lane >> 4) & 1;
+
+    // this lane's query column
+    const int qi = q0 + wave * 32 + l32;
+    const bool qvalid = qi < rows;
+    const int r = qvalid ? quot(a.by_grp, qi) : 0;
+    const int hq = h * grp + (qvalid ? qi - r * grp : 0);
+    u32x4 qf[DS];
+    const char *qrow = static_cast<const char *>(a.q) + ((static_cast<int64_t>(b) * a.n_q + r) * a.Hq + hq) * D * 2;
+#pragma unroll
+    for (int s = 0; s < DS; ++s) qf[s] = *reinterpret_cast<const u32x4 *>(qrow + (16 * s + 8 * g) * 2);
+
+    const int lc = uniform(max(a.ctx_len[b], 0));
+    const int ln = static_cast<int>(min(static_cast<int64_t>(lc) + 2 * a.K + 3, static_cast<int64_t>(a.L)));
+    const int qs = uniform(a.q_start[b]);
+    const int r_hi = min(q0 + kWideRows, rows) - 1;
+    const int p_lo = qs + static_cast<int>(quot(a.by_grp, q0));
+    const int p_hi = qs + static_cast<int>(quot(a.by_grp, r_hi));
+    const int kend = uniform(p_lo >= ln ? 0 : p_hi >= lc ? ln : min(p_hi + 1, ln));   // all padding: no key
+    const int p = qs + r;
+    const bool live = qvalid && p >= 0 && p < ln;
+    const int vis = p < lc ? p + 1 : ln;                   // keys [0, vis) are visible
+    // scores are taken as |scale| * (+-q) . k: the largest product is then the largest score
+    const uint32_t flip = a.scale < 0.f ? 0x80008000u : 0u;
+    const float sc = fmaxf(fabsf(a.scale) * kLog2eA, 1.17549435e-38f);
+#pragma unroll
+    for (int s = 0; s < DS; ++s) {
+        asm volatile("" : "+v"(qf[s]));
+#pragma unroll
+        for (int w = 0; w < 4; ++w) qf[s][w] = live ? qf[s][w] ^ flip : 0u;
+    }
+    int vis_min = live ? vis : INT_MAX;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) vis_min = min(vis_min, __shfl_xor(vis_min, off));
+
+    floatx16 o[DT];
+#pragma unroll
+    for (int t = 0; t < DT; ++t)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[t][i] = 0.f;
+    float m = -INFINITY, l = 0.f;
+
+    const uint32_t row_b = static_cast<uint32_t>(a.Hkv) * D * 2;
+    const int64_t head0 = (static_cast<int64_t>(b) * a.L * a.Hkv + h) * D * 2;
+    const int nbytes = kend > 0 ? static_cast<int>((kend - 1) * row_b + RB) : 0;
+    const u32x4 krs = raw_rsrc(static_cast<const char *>(a.k) + head0, nbytes);
+    const u32x4 vrs = raw_rsrc(static_cast<const char *>(a.v) + head0, nbytes);
+    uint32_t koff[LPW], voff[LPW];
+#pragma unroll
+    for (int q = 0; q < LPW; ++q) {
+        const int o16 = ((wave * LPW + q) * 1024 + lane * 16);
+        const int lrow = o16 / RB, pch = (o16 % RB) / 16;
+        koff[q] = lrow * row_b + (pch ^ swz_k<RB>(lrow)) * 16;
+        voff[q] = lrow * row_b + (((pch >> 1) ^ swz_vw<RB>(lrow)) * 2 + (pch & 1)) * 16;
+    }
+    const int nblk = (kend + kWideKeys - 1) / kWideKeys;
+    const uint32_t lds_k = uniform(lds_addr(s_k[0]) + wave * LPW * 1024);
+    const uint32_t lds_v = uniform(lds_addr(s_v[0]) + wave * LPW * 1024);
+    auto issue = [&](int j) {
+        const uint32_t off = static_cast<uint32_t>(j * kWideKeys) * row_b, slot = (j & 1) * SB;
+#pragma unroll
+        for (int q = 0; q < LPW; ++q) load_lds16_asm(krs, koff[q] + off, lds_k + slot + q * 1024);
+#pragma unroll
+        for (int q = 0; q < LPW; ++q) load_lds16_asm(vrs, voff[q] + off, lds_v + slot + q * 1024);
+    };
+    // LDS addresses of this lane's fragments within a stage: the swizzles depend on the row
+    // modulo 16 (keys) and 8 (values) only, so the rest is a constant offset of the read
+    uint32_t ka[DS], va[DT];
+#pragma unroll
+    for (int s = 0; s < DS; ++s) ka[s] = l32 * RB + ((2 * s + g) ^ swz_k<RB>(l32)) * 16;
+    const int vrow = 4 * g + (l16 >> 2);
+#pragma unroll
+    for (int t = 0; t < DT; ++t) va[t] = vrow * RB + ((2 * t + dh) ^ swz_vw<RB>(vrow)) * 32 + 8 * (l16 & 3);
+
+    if (nblk > 0) issue(0);
+    for (int j = 0; j < nblk; ++j) {
+        wait_vm<0>();                                       // this wave's loads of stage j
+        lds_barrier();                                      // stage j landed; stage j-1 consumed
+        if (j + 1 < nblk) issue(j + 1);
+        const char *sk = s_k[0] + (j & 1) * SB, *sv = s_v[0] + (j & 1) * SB;
+        const int k0 = j * kWideKeys;
+
+        // S^T[key][query]: element i of tile c is key 32c + 8 (i / 4) + 4g + i % 4
+        floatx16 st[KT];
+#pragma unroll
+        for (int c = 0; c < KT; ++c) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) st[c][i] = 0.f;
+#pragma unroll
+            for (int s = 0; s < DS; ++s)
+                st[c] = mfma32(*reinterpret_cast<const u32x4 *>(sk + ka[s] + 32 * c * RB), qf[s], st[c]);
+        }
+        if (k0 + kWideKeys > vis_min) {                      // wave-uniform: some key is masked
+#pragma unroll
+            for (int c = 0; c < KT; ++c)
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (k0 + 32 * c + 8 * (i / 4) + 4 * g + i % 4 >= vis) st[c][i] = -INFINITY;
+        }
+        float bm = -INFINITY;
+#pragma unroll
+        for (int c = 0; c < KT; ++c)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) bm = fmaxf(bm, st[c][i]);
+        {
+            const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(bm), __float_as_uint(bm), false, false);
+            bm = fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1])) * sc;
+        }
+        const bool raise = bm > m + kLazyRescale;
+        if (__builtin_expect(__ballot(raise) != 0, 0)) {
+            const float alpha = raise ? __builtin_amdgcn_exp2f(m - bm) : 1.f;
+            if (raise) m = bm;
+            l *= alpha;
+#pragma unroll
+            for (int t = 0; t < DT; ++t)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) o[t][i] *= alpha;
+        }
+        const float mm = m == -INFINITY ? INFINITY : m;     // nothing visible yet: every weight 0
+        uint32_t pk[KT][8];
+#pragma unroll
+        for (int c = 0; c < KT; ++c)
+#pragma unroll
+            for (int i = 0; i < 16; i += 2) {
+                const float p0 = __builtin_amdgcn_exp2f(fmaf(st[c][i], sc, -mm));
+                const float p1 = __builtin_amdgcn_exp2f(fmaf(st[c][i + 1], sc, -mm));
+                l += p0 + p1;
+                pk[c][i / 2] = bf16_pair(p0, p1);
+            }
+        // O^T[d][query] += V^T[d][keys] P^T[keys][query], sixteen keys per product: lane
+        // group g holds keys 4g + 0..3 and 8 + 4g + 0..3 of them in P, and the transposing
+        // reads give the same keys of V column 32t + lane % 32.
+#pragma unroll
+        for (int c = 0; c < KT; ++c)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const u32x4 pb{pk[c][4 * u], pk[c][4 * u + 1], pk[c][4 * u + 2], pk[c][4 * u + 3]};
+#pragma unroll
+                for (int t = 0; t < DT; ++t) {
+                    const u32x2 lo = read_tr_tracked(sv + va[t] + (32 * c + 16 * u) * RB);
+                    const u32x2 hi = read_tr_tracked(sv + va[t] + (32 * c + 16 * u + 8) * RB);
+                    o[t] = mfma32(u32x4{lo[0], lo[1], hi[0], hi[1]}, pb, o[t]);
+                }
+            }
+    }
+
+    {
+        const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l), false, false);
+        l = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+    }
+    if (!qvalid) return;
+    // O^T tile t, elements 4e .. 4e + 3: d = 32t + 8e + 4g + 0..3 of this lane's query
+    char *orow = static_cast<char *>(a.out) + ((static_cast<int64_t>(b) * a.n_q + r) * a.Hq + hq) * D * 2;
+    const float inv = live && l > 0.f ? 1.f / l : 0.f;
+#pragma unroll
+    for (int t = 0; t < DT; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t w0 = bf16_pair(o[t][4 * e] * inv, o[t][4 * e + 1] * inv);
+            const uint32_t w1 = bf16_pair(o[t][4 * e + 2] * inv, o[t][4 * e + 3] * inv);
+            *reinterpret_cast<u32x2 *>(orow + (32 * t + 8 * e + 4 * g) * 2) = u32x2{w0, w1};
+        }
+}
+
 // One wave per query row: merges the row's pieces.  The pieces that hold a key the row
 // sees are [0, ceil(vis / chunk)); lane s weighs piece s (at most 64), then D / 4 lanes
 // take one piece's four output columns each, 64 / (D / 4) pieces side by side.
@@ -456,6 +713,9 @@ int64_t attn_waves(int64_t rows) {
     return std::max<int64_t>(4, (((rows + nwg - 1) / nwg) + 15) / 16);
 }
 
+// Query rows of a group from which the wide kernel runs: what no longer fits one workgroup
+// of the 16-row kernel (64 groups-of-8 x 132 rows x 2081 keys: 156 us there, 127 wide).
+constexpr int64_t kWideMinRows = 129;
 constexpr int64_t kCus = 256;         // compute units of an MI355X
 constexpr int64_t kMinChunk = 128;    // keys of a piece, at least
 
@@ -523,6 +783,21 @@ hipError_t launch_hybrid_attention(AttnArgs a, hipStream_t s) {
             hipLaunchKernelGGL((k_hybrid_attention<64, true>), grid, block, 0, s, a);
             hipLaunchKernelGGL(k_attention_combine<64>, cgrid, dim3(256), 0, s, a);
         }
+        return hipGetLastError();
+    }
+    if (rows >= kWideMinRows) {
+        const int64_t groups = static_cast<int64_t>(a.B) * a.Hkv;
+        const int64_t xcds = groups % kXcds == 0 ? kXcds : 1;
+        const int64_t tiles = (rows + kWideRows - 1) / kWideRows;
+        // 4 sequences x 2065 positions, 32/8 heads: 136 us tile by tile, 109 us group by
+        // group; 16 x 317, 8/8 heads (384 workgroups, two to a CU): 13.7 against 15.4 us
+        const bool by_tile = groups * tiles <= 2 * kCus;
+        a.by_wgs = fast_div(static_cast<uint32_t>(by_tile ? groups / xcds : tiles));
+        a.chunk = by_tile;
+        a.splits = static_cast<int32_t>(xcds);
+        const dim3 wgrid(static_cast<unsigned>(groups * tiles));
+        if (a.D == 128) hipLaunchKernelGGL(k_hybrid_attention_wide<128>, wgrid, dim3(64 * kWideWaves), 0, s, a);
+        else hipLaunchKernelGGL(k_hybrid_attention_wide<64>, wgrid, dim3(64 * kWideWaves), 0, s, a);
         return hipGetLastError();
     }
     const dim3 grid(static_cast<unsigned>(wgs));

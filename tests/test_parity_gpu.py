@@ -1022,3 +1022,27 @@ def test_hybrid_attention_pieces_match_uncut():
     cut = cs.hybrid_attention(q, k, v, ctx, ctx, K, 0.09)
     # each side's weights are rounded to bf16 (2^-9), its result too: 4 * 2^-9 of max |v|
     assert (out.float() - cut.float()).abs().max().item() <= 4 * 2.0 ** -9 * v.float().abs().max().item()
+
+
+@pytest.mark.parametrize("B,nq,Hq,Hkv,D,L,ctx,K,qs", [
+    (1, 129, 1, 1, 128, 200, [150], 5, [0]),            # one row past a tile of 128
+    (8, 64, 8, 2, 128, 63, [40] * 8, 3, [0] * 8),       # two tiles exactly, groups dealt to the XCDs, one short block
+    (2, 140, 3, 1, 64, 140, [64, 127], 4, [0, 0]),      # keys end at and beside a block of 64; three heads per group
+    (3, 200, 4, 1, 128, 260, [190, 5, 0], 6, [0, 0, 30]),   # tiles of padding rows, queries that start inside
+    (2, 96, 4, 2, 64, 130, [65, 110], 2, [40, 3]),      # starts inside the input, ends past it
+    (70, 40, 32, 8, 128, 70, [(7 * b) % 60 for b in range(70)], 4, [0] * 70),   # more workgroups than fit at once
+])
+def test_hybrid_attention_many_rows(B, nq, Hq, Hkv, D, L, ctx, K, qs):
+    _attn_case(B, nq, Hq, Hkv, D, L, ctx, qs, K, seed=nq)
+
+
+@pytest.mark.parametrize("scale", [-0.11, 0.0])
+def test_hybrid_attention_many_rows_scale(scale):
+    # a negative scale reverses the order of the scores; with scale 0 every visible key weighs the same
+    B, n, Hq, Hkv, D, K, ctx = 1, 160, 2, 2, 64, 3, 140
+    g = torch.Generator().manual_seed(31)
+    q, k, v = (torch.randn(B, n, h, D, generator=g).to(torch.bfloat16) for h in (Hq, Hkv, Hkv))
+    c = torch.tensor([ctx], dtype=torch.int32)
+    got = cs.hybrid_attention(q.to(DEV), k.to(DEV), v.to(DEV), c.to(DEV), torch.zeros_like(c).to(DEV), K, scale)
+    ref = oracle.hybrid_attention(bf16_bits(q), bf16_bits(k), bf16_bits(v), [ctx], [0], K, scale)
+    assert np.abs(got.float().cpu().numpy() - ref).max() <= 6e-3 * float(v.float().abs().max())
