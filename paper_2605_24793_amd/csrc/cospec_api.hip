@@ -77,11 +77,10 @@ inline int32_t ksplit_for(int64_t m_cap, const cospec_head *hd) {
     return hd ? head_ksplit(m_cap, hd->d, hd->h, elem_bytes(hd->dtype)) : 0;   // no head: no scratch
 }
 
-// Head scratch: k-slice partial pre-activations and the logits.
+// cospec_arbitrate's scratch: k-slice partial pre-activations.
 inline size_t head_bytes(int64_t m_cap, const cospec_head *hd) {
     return round_up(static_cast<size_t>(ksplit_for(m_cap, hd)) * static_cast<size_t>(m_cap) *
-                    static_cast<size_t>(hd->h) * 4) +
-           round_up(static_cast<size_t>(m_cap) * 4);
+                    static_cast<size_t>(hd->h) * 4);
 }
 
 // Workspace carving shared by the size query and the call.
@@ -406,7 +405,7 @@ cospec_status run(const Common &c, Phase phase, int32_t *accept_len, int32_t *ou
         const Dtype hdt = static_cast<Dtype>(c.head->dtype);
         const hipError_t he = every_slot ? launch_slot_gemm(hdt, ha, c.stream)
                               : fuse_head ? launch_head_gemm(hdt, ha, c.stream)
-                                          : launch_head(hdt, ha, c.stream);
+                                          : launch_head(hdt, ha, nullptr, c.stream);
         if (he != hipSuccess) return COSPEC_ERR_HIP;
     }
 
@@ -838,8 +837,6 @@ cospec_status cospec_arbitrate(const void *hidden, int64_t n_rows, const int32_t
 
     const int32_t ks = ksplit_for(n_sel, head);
     float *upart = static_cast<float *>(workspace);
-    float *zlog = reinterpret_cast<float *>(static_cast<char *>(workspace) +
-                                            round_up(static_cast<size_t>(ks) * n_sel * head->h * 4));
     HeadArgs ha{};
     ha.hidden = hidden; ha.n_rows = n_rows; ha.list = row_index;
     ha.count_dev = nullptr; ha.count_host = n_sel; ha.m_cap = n_sel;
@@ -850,12 +847,8 @@ cospec_status cospec_arbitrate(const void *hidden, int64_t n_rows, const int32_t
     ha.two_per_cu = ((n_sel + kHeadTileM - 1) / kHeadTileM) * ((head->h + kHeadTileN - 1) / kHeadTileN) * ks >
                     cu_count();
     ha.upart = upart;
-    ha.z = zlog;
-    if (launch_head(static_cast<Dtype>(head->dtype), ha, stream) != hipSuccess) return COSPEC_ERR_HIP;
-    ArbFinishArgs fa{};
-    fa.n_sel = n_sel; fa.n_rows = n_rows; fa.row_index = row_index;
-    fa.z = zlog; fa.lambda = lambda; fa.out_z = out_z; fa.out_accept = out_accept;
-    if (launch_arb_finish(fa, stream) != hipSuccess) return COSPEC_ERR_HIP;
+    const ArbOut out{out_z, out_accept, lambda};
+    if (launch_head(static_cast<Dtype>(head->dtype), ha, &out, stream) != hipSuccess) return COSPEC_ERR_HIP;
     return COSPEC_OK;
 }
 

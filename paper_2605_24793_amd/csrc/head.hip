@@ -515,36 +515,32 @@ __global__ __launch_bounds__(kReduceThreads) void k_slot_gemm(HeadArgs a) {
     slotgemm::run<DT>(a, blockIdx.x, reinterpret_cast<const u32x4 *>(kZeroVec));
 }
 
-// z[m] = w2 . relu(sum_ks upart[ks][m] + b1) + b2, one wave per row, fixed order.
-template <int DT>
-__global__ __launch_bounds__(256) void k_head_epilogue(HeadArgs a) {
+// z[m] = w2 . relu(sum_ks upart[ks][m] + b1) + b2, one wave per row, fixed order.  ARB
+// (cospec_arbitrate): z goes to the caller with its threshold decision; an index outside
+// [0, n_rows) has z = NaN and accept 0.
+template <int DT, bool ARB>
+__global__ __launch_bounds__(256) void k_head_epilogue(HeadArgs a, ArbOut o) {
     const int64_t M = a.count_dev ? static_cast<int64_t>(*a.count_dev) : a.count_host;
     const int64_t m = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (m >= M) return;
     const float z = headz::head_z<DT>(a, m, threadIdx.x & 63, a.ksplit);
-    if ((threadIdx.x & 63) == 0) a.z[m] = z;
-}
-
-__global__ __launch_bounds__(256) void k_arb_finish(ArbFinishArgs a) {
-    const int64_t k = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (k >= a.n_sel) return;
-    const int64_t r = a.row_index ? static_cast<int64_t>(a.row_index[k]) : k;
-    float z = NAN;
-    uint8_t acc = 0;
-    if (r >= 0 && r < a.n_rows) {
-        z = a.z[k];
-        const float pi = 1.0f / (1.0f + expf(-z));
-        acc = pi > a.lambda;
+    if ((threadIdx.x & 63) != 0) return;
+    if constexpr (ARB) {
+        if (o.z) o.z[m] = z;
+        if (o.accept) o.accept[m] = 1.0f / (1.0f + expf(-z)) > o.lambda;
+    } else {
+        a.z[m] = z;
     }
-    if (a.out_z) a.out_z[k] = z;
-    if (a.out_accept) a.out_accept[k] = acc;
 }
 
 }  // namespace
 
 // k-slices of d: one per XCD (each XCD's L2 then holds one slice of the hidden rows
 // and of W1), more, in multiples of the XCD count, while the tiles times slices stay
-// below one workgroup per CU; never more than there are stages of d.
+// below one workgroup per CU; fewer when the tiles alone give every CU two workgroups of
+// the shallow ring, so that no more partials are written and read back than that takes
+// (4096 rows, 5120 -> 512, 128 tiles: GEMM + second layer 36.4 + 13.4 us in 8 slices, 26.5 +
+// 8.9 in 4, 29.1 + 7.7 in 2, 45.2 + 7.2 in 1); never more than there are stages of d.
 int32_t head_ksplit(int64_t m_cap, int32_t d, int32_t h, int32_t elem_bytes) {
     const int64_t mt = (m_cap + kHeadTileM - 1) / kHeadTileM;
     const int64_t nt = (h + kHeadTileN - 1) / kHeadTileN;
@@ -552,6 +548,7 @@ int32_t head_ksplit(int64_t m_cap, int32_t d, int32_t h, int32_t elem_bytes) {
     const int64_t stages = (static_cast<int64_t>(d) * elem_bytes + kStageBytes - 1) / kStageBytes;
     int64_t ks = kXcds;
     while (ks + kXcds <= kHeadMaxSplit && mt * nt * (ks + kXcds) <= kHeadTargetBlocks) ks += kXcds;
+    if (mt * nt * ks > kHeadMostBlocks) ks = kHeadMostBlocks / (mt * nt);
     if (ks > stages) ks = stages;
     if (ks < 1) ks = 1;
     return static_cast<int32_t>(ks);
@@ -627,20 +624,19 @@ hipError_t launch_head_gemm(Dtype dt, const HeadArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_head(Dtype dt, const HeadArgs &a, hipStream_t s) {
-    const dim3 egrid(static_cast<unsigned>((a.m_cap + 3) / 4));
+hipError_t launch_head(Dtype dt, const HeadArgs &a, const ArbOut *out, hipStream_t s) {
+    const dim3 egrid(static_cast<unsigned>((a.m_cap + 3) / 4)), block(256);
     if (egrid.x == 0) return hipSuccess;
     const hipError_t e = launch_head_gemm(dt, a, s);
     if (e != hipSuccess) return e;
-    if (dt == kBF16) hipLaunchKernelGGL(k_head_epilogue<kBF16>, egrid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL(k_head_epilogue<kF32>, egrid, dim3(256), 0, s, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_arb_finish(const ArbFinishArgs &a, hipStream_t s) {
-    const unsigned blocks = static_cast<unsigned>((a.n_sel + 255) / 256);
-    if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_arb_finish, dim3(blocks), dim3(256), 0, s, a);
+    const ArbOut o = out ? *out : ArbOut{};
+    if (dt == kBF16) {
+        if (out) hipLaunchKernelGGL((k_head_epilogue<kBF16, true>), egrid, block, 0, s, a, o);
+        else hipLaunchKernelGGL((k_head_epilogue<kBF16, false>), egrid, block, 0, s, a, o);
+    } else {
+        if (out) hipLaunchKernelGGL((k_head_epilogue<kF32, true>), egrid, block, 0, s, a, o);
+        else hipLaunchKernelGGL((k_head_epilogue<kF32, false>), egrid, block, 0, s, a, o);
+    }
     return hipGetLastError();
 }
 

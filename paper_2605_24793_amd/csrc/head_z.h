@@ -44,15 +44,15 @@ __device__ inline int live_ksplit(const HeadArgs &a, int64_t M) {
 }
 
 // One pass of a lane covers CPL columns (lane, lane + 64, ...) and loads SPL k-slice
-// partials of each together, CPL * SPL = 64 loads in flight; narrow heads take fewer
-// columns and more slices per pass.  Every load of a pass is unconditional (indexes
-// past the end are clamped and their values dropped), b1 and w2 included, so that none
-// waits for another.  The partials are read once: nontemporal loads keep them from
-// displacing W1 in L2, which the next step's GEMM reads again (measured: the large
-// chain batch's GEMM 15.7 -> 13.8 us).
-template <int DT, int CPL>
+// partials of each together; narrow heads take fewer columns and more slices per pass,
+// few slices no more than there are (loads clamped to an earlier slice still cost their
+// issue: 4096 rows, h = 512, 4 slices, 8.9 us with eight slices a pass, 8.0 with four).
+// Every load of a pass is unconditional (indexes past the end are clamped and their values
+// dropped), b1 and w2 included, so that none waits for another.  The partials are read
+// once: nontemporal loads keep them from displacing W1 in L2, which the next step's GEMM
+// reads again (measured: the large chain batch's GEMM 15.7 -> 13.8 us).
+template <int DT, int CPL, int SPL>
 __device__ inline float head_z_cols(const HeadArgs &a, int64_t m, int lane, int ksplit) {
-    constexpr int SPL = 64 / CPL;
     const void *b1 = a.b1 ? a.b1 : a.w2;                  // no bias: read w2, use 0
     float acc = 0.f;
     for (int n0 = 0; n0 < a.h; n0 += 64 * CPL) {
@@ -97,7 +97,9 @@ __device__ inline float head_z_cols(const HeadArgs &a, int64_t m, int lane, int 
 // k-slices are summed in slice order.
 template <int DT>
 __device__ inline float head_z(const HeadArgs &a, int64_t m, int lane, int ksplit) {
-    const float acc = a.h <= 256 ? head_z_cols<DT, 4>(a, m, lane, ksplit) : head_z_cols<DT, 8>(a, m, lane, ksplit);
+    float acc;
+    if (a.h <= 256) acc = ksplit <= 4 ? head_z_cols<DT, 4, 4>(a, m, lane, ksplit) : head_z_cols<DT, 4, 16>(a, m, lane, ksplit);
+    else acc = ksplit <= 4 ? head_z_cols<DT, 8, 4>(a, m, lane, ksplit) : head_z_cols<DT, 8, 8>(a, m, lane, ksplit);
     const int64_t id = hidden_row(a, m);
     return id >= 0 && id < a.n_rows ? acc + a.b2 : NAN;
 }

@@ -16,6 +16,7 @@ constexpr int kHeadTileN = 128;       //                            columns of W
 // per step; 256 gained less and cost the large chain batch 0.5 us)
 constexpr int kHeadTargetBlocks = 128;
 constexpr int kHeadMaxSplit = 32;
+constexpr int kHeadMostBlocks = 512;  // slices are taken off while the grid exceeds two workgroups per CU
 constexpr int kXcds = 8;             // MI355X: 8 XCDs, each with its own L2
 constexpr int kMaxSeqRows = 256;      // rows per sequence / nodes per tree held in LDS
 constexpr int kSegVecs = 64;          // 16-byte vectors per probability-mass segment (one wave load)
@@ -261,12 +262,11 @@ struct AttnPlan {
     int64_t rows;              // B * n_q * Hq when the keys are cut, else 0
 };
 
-struct ArbFinishArgs {
-    int64_t n_sel, n_rows;
-    const int32_t *row_index;
-    const float *z;
+// Outputs of cospec_arbitrate (either may be null).
+struct ArbOut {
+    float *z;
+    uint8_t *accept;
     float lambda;
-    float *out_z; uint8_t *out_accept;
 };
 
 hipError_t launch_reduce(Dtype dt, const ReduceArgs &a, hipStream_t s);
@@ -277,14 +277,14 @@ int32_t reduce_slots(Dtype dt);   // reduction workgroups resident at once on th
 hipError_t launch_sample(Dtype dt, const SampleArgs &a, hipStream_t s);
 hipError_t launch_decide(Dtype dt, const DecideArgs &a, hipStream_t s);
 int32_t head_ksplit(int64_t m_cap, int32_t d, int32_t h, int32_t elem_bytes);
-hipError_t launch_head(Dtype dt, const HeadArgs &a, hipStream_t s);   // GEMM + epilogue
+// GEMM + epilogue: z of the listed rows, or cospec_arbitrate's outputs when out is given.
+hipError_t launch_head(Dtype dt, const HeadArgs &a, const ArbOut *out, hipStream_t s);
 hipError_t launch_head_gemm(Dtype dt, const HeadArgs &a, hipStream_t s);
 // The first layer over all a.m_cap decision slots on its own (slot_gemm.h).
 hipError_t launch_slot_gemm(Dtype dt, const HeadArgs &a, hipStream_t s);
 // Resident workgroups of the persistent head GEMM on the current device (cached).
 int32_t head_gemm_slots(Dtype dt, bool build);   // GEMM only
 hipError_t launch_finish(Dtype dt, const FinishArgs &a, hipStream_t s);
-hipError_t launch_arb_finish(const ArbFinishArgs &a, hipStream_t s);
 hipError_t launch_sps(Dtype dt, const SpsArgs &a, hipStream_t s);   // finish, weights, pick
 hipError_t launch_hybrid_mask(const MaskArgs &a, hipStream_t s);
 AttnPlan attn_plan(int32_t B, int32_t n_q, int32_t L, int32_t Hq, int32_t Hkv, int32_t D);

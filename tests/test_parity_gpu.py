@@ -1046,3 +1046,33 @@ def test_hybrid_attention_many_rows_scale(scale):
     got = cs.hybrid_attention(q.to(DEV), k.to(DEV), v.to(DEV), c.to(DEV), torch.zeros_like(c).to(DEV), K, scale)
     ref = oracle.hybrid_attention(bf16_bits(q), bf16_bits(k), bf16_bits(v), [ctx], [0], K, scale)
     assert np.abs(got.float().cpu().numpy() - ref).max() <= 6e-3 * float(v.float().abs().max())
+
+
+@pytest.mark.parametrize("n,d,h,dtype", [
+    (16384 + 5, 64, 128, "bf16"),      # 129 row tiles: 3 k-slices, but only one stage of d
+    (8193, 512, 130, "bf16"),          # 65 x 2 tiles: 3 slices
+    (4097, 264, 300, "f32"),           # 33 x 3 tiles of a wide fp32 head: 5 slices, a ragged last one
+    (1, 64, 1, "bf16"),                # one row, one column
+    (129, 4096, 512, "bf16"),          # few tiles: 16 slices
+])
+def test_arbitrate_slices(n, d, h, dtype):
+    # how many k-slices a call takes depends on its row count; z against float64, NaN and a
+    # rejection at indices off either end
+    g = torch.Generator().manual_seed(n)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    hid = torch.randn(n, d, generator=g).to(dt)
+    w1 = (torch.randn(h, d, generator=g) / d ** 0.5).to(dt)
+    b1, w2 = torch.randn(h, generator=g).to(dt), (torch.randn(h, generator=g) / h ** 0.5).to(dt)
+    idx = torch.randint(0, n, (n,), generator=g).to(torch.int32)
+    idx[0], idx[-1] = (-1, n) if n > 1 else (0, 0)
+    head = workloads.Head(w1.to(DEV), b1.to(DEV), w2.to(DEV), 0.25)
+    out = cs.arbitrate(hid.to(DEV), head, 0.5, row_index=idx.to(DEV))
+    ok = (idx >= 0) & (idx < n)
+    x = hid.double()[idx.clamp(0, n - 1).long()]
+    ref = (x @ w1.double().t() + b1.double()).clamp(min=0) @ w2.double() + 0.25
+    z, acc = out["z"].cpu().double(), out["accept"].cpu()
+    assert torch.isnan(z[~ok]).all() and (acc[~ok] == 0).all()
+    # fp32 sums of d, then h, products of size about 1: |error| below 2^-24 * (d + h) in the worst order
+    assert (z[ok] - ref[ok]).abs().max() <= 2.0 ** -24 * (d + h) * max(1.0, float(ref.abs().max()))
+    clear = ok & ((torch.sigmoid(ref) - 0.5).abs() > 1e-3)
+    assert torch.equal(acc[clear].bool(), torch.sigmoid(ref[clear]) > 0.5)
