@@ -1076,3 +1076,13 @@ def test_arbitrate_slices(n, d, h, dtype):
     assert (z[ok] - ref[ok]).abs().max() <= 2.0 ** -24 * (d + h) * max(1.0, float(ref.abs().max()))
     clear = ok & ((torch.sigmoid(ref) - 0.5).abs() > 1e-3)
     assert torch.equal(acc[clear].bool(), torch.sigmoid(ref[clear]) > 0.5)
+
+
+@pytest.mark.parametrize("B,K,noise", [(40, 11, 0.9), (24, 12, 0.9), (12, 22, 3.0), (12, 23, 0.2), (5, 64, 1.5)])
+def test_chain_finish_slots_per_wave(B, K, noise):
+    # the finish's eleven head waves take one, two or more slots each; more than 256 decision
+    # slots, so that only the mismatches are scored (few of them, or nearly all)
+    wl = workloads.make_chain(B=B, K=K, V=5003, d=64, h=32, dtype="bf16", seed=K, bias=True, noise=noise)
+    assert B * K > 256
+    gpu = _gpu_block(wl, 0.5)
+    parity.check_block(gpu, _ref_block(wl, 0.5))
