@@ -523,7 +523,7 @@ __global__ __launch_bounds__(256) void k_head_epilogue(HeadArgs a, ArbOut o) {
     const int64_t M = a.count_dev ? static_cast<int64_t>(*a.count_dev) : a.count_host;
     const int64_t m = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (m >= M) return;
-    const float z = headz::head_z<DT>(a, m, threadIdx.x & 63, a.ksplit);
+    const float z = headz::head_z<DT, true>(a, m, threadIdx.x & 63, a.ksplit);
     if ((threadIdx.x & 63) != 0) return;
     if constexpr (ARB) {
         if (o.z) o.z[m] = z;

@@ -94,12 +94,14 @@ __device__ inline float head_z_cols(const HeadArgs &a, int64_t m, int lane, int 
 
 // z of list entry m, in every lane of the calling wave, from the first `ksplit`
 // k-slices of upart; NaN when its hidden row is outside [0, n_rows).  Each column's
-// k-slices are summed in slice order.
-template <int DT>
+// k-slices are summed in slice order.  FEW: also has the form for at most four slices (the
+// chain finish goes without: its slices are rarely so few, and the extra code cost the
+// 8 x K=5 step 0.3 us).
+template <int DT, bool FEW>
 __device__ inline float head_z(const HeadArgs &a, int64_t m, int lane, int ksplit) {
     float acc;
-    if (a.h <= 256) acc = ksplit <= 4 ? head_z_cols<DT, 4, 4>(a, m, lane, ksplit) : head_z_cols<DT, 4, 16>(a, m, lane, ksplit);
-    else acc = ksplit <= 4 ? head_z_cols<DT, 8, 4>(a, m, lane, ksplit) : head_z_cols<DT, 8, 8>(a, m, lane, ksplit);
+    if (FEW && ksplit <= 4) acc = a.h <= 256 ? head_z_cols<DT, 4, 4>(a, m, lane, ksplit) : head_z_cols<DT, 8, 4>(a, m, lane, ksplit);
+    else acc = a.h <= 256 ? head_z_cols<DT, 4, 16>(a, m, lane, ksplit) : head_z_cols<DT, 8, 8>(a, m, lane, ksplit);
     const int64_t id = hidden_row(a, m);
     return id >= 0 && id < a.n_rows ? acc + a.b2 : NAN;
 }
