@@ -26,6 +26,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 # Chain batches of at most this many decision slots run the head's first layer in the
 # reduction's launch (kEverySlotMax in paper_2605_24793_amd/csrc/cospec_api.hip).
 EVERY_SLOT_MAX = 256
+# ... and with a bf16 head, from this many slots (kTilesMinSlots there) and up to this many
+# tiles of 64 slots x 64 columns, in tiles in that launch.
+TILES_MIN_SLOTS, TILES_MAX = 49, 128
 sys.path.insert(0, ROOT)
 
 METRIC = "verified rows/sec (B×(k+1)) and achieved HBM GB/s vs peak, V=151936 bf16"
@@ -259,6 +262,10 @@ class Step:
             # the library runs the head's first layer over every decision slot in the
             # reduction's launch: the timed launch holds both
             self.kernel = "k_vocab_reduce_head (reduction + the head's first layer on every slot)"
+        slots = 0 if self.tree or sps_u is not None else wl.B * wl.K
+        tiles = -(-slots // 64) * -(-wl.head.h // 64)
+        if slots >= TILES_MIN_SLOTS and tiles <= TILES_MAX and wl.head.w1.dtype == torch.bfloat16 and wl.head.d >= 449:
+            self.kernel = "k_vocab_reduce_tiles (reduction + the head's first layer in tiles)"
         self.logit_bytes = self.reduced_rows * wl.V * self.elem   # algorithmic bytes of the reductions
         self.step = self.p.launch
 

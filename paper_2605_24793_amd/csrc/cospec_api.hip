@@ -45,7 +45,8 @@ namespace {
 constexpr size_t kAlign = 256;
 constexpr int64_t kMinPartialSlots = 16384;   // room for a split override on small batches
 constexpr int64_t kMaxRowBytes = INT32_MAX;    // V * element bytes of one logit row
-// Chain batches with at most this many decision slots run the head's first layer on
+// Chain batches with at most this many decision slots, when they do not run it in tiles
+// (head_tile_groups below: bf16 heads from kTilesMinSlots slots), run the head's first layer on
 // every slot (slot_gemm.h) rather than on the mismatch rows after the reduction, in at
 // most kEverySlotSplits k-slices (fewer partials for the finish to add; the slot GEMM's
 // extra k-steps hide behind the reduction).  Measured on MI355X, step times: B=8 K=5
@@ -54,6 +55,10 @@ constexpr int64_t kMaxRowBytes = INT32_MAX;    // V * element bytes of one logit
 // K=7 (448 slots) 65.6 us on the mismatch rows, 66.8 on every slot.
 constexpr int64_t kEverySlotMax = 256;
 constexpr int32_t kEverySlotSplits = 16;
+// From this many slots on, a bf16 head runs in 64 x 64 tiles there instead (tile_gemm.h): 16 x
+// K=4 (64 slots) 18.4 -> 17.4 us, 3 x K=20 (60) with h = 320 24.5 -> 17.3, but 8 x K=5 (40) 14.6 ->
+// 15.3 and 4 x K=7 (28) 17.8 -> 18.1.
+constexpr int64_t kTilesMinSlots = 49;
 
 inline size_t round_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
@@ -81,6 +86,24 @@ inline int32_t ksplit_for(int64_t m_cap, const cospec_head *hd) {
 inline size_t head_bytes(int64_t m_cap, const cospec_head *hd) {
     return round_up(static_cast<size_t>(ksplit_for(m_cap, hd)) * static_cast<size_t>(m_cap) *
                     static_cast<size_t>(hd->h) * 4);
+}
+
+// Chain batches whose head's first layer runs in tiles over every decision slot, beside the
+// reduction (tile_gemm.h): the slice groups a tile's workgroups share out (1, 2, 4 or 8; 0: not
+// in tiles).  bf16 heads only.  As many groups as keep the tiles' workgroups at one per CU:
+// more displace the reduction, fewer end after it (64 x K=7, 28 tiles: 54.4 us with 4 groups,
+// 55.6 with 8, 61.8 with 2, 65.4 on the mismatch rows after the reduction; 48 x K=10, 5120 ->
+// 512, 64 tiles: 56.2 with 4, 61.1 with 8, 69.0 after; 128 x K=7, 5120 -> 512, 112 tiles: 104.3
+// with 2, 110.2 with 4, 115.8 after).  From 129 tiles on a group would be all of d, and the
+// tiles outlast the reduction (256 x K=7, 5120 -> 512, 224 tiles: 195 either way).
+int32_t head_tile_groups(int64_t m_cap, const cospec_head *hd) {
+    if (hd->dtype != COSPEC_BF16 || m_cap < kTilesMinSlots) return 0;
+    const int64_t tiles = (m_cap + kHeadSmallTile - 1) / kHeadSmallTile * ((hd->h + kHeadSmallTile - 1) / kHeadSmallTile);
+    // the partials of the eight slices of the form on its own need their place
+    if (tiles > 128 || ksplit_for(m_cap, hd) < kHeadTileSlices) return 0;
+    int32_t groups = kHeadTileSlices;
+    while (tiles * groups > 256) groups /= 2;
+    return groups;
 }
 
 // Workspace carving shared by the size query and the call.
@@ -173,11 +196,19 @@ int64_t split_vectors(int64_t nvec, int32_t splits, bool segments) {
 }
 
 // The partial layout of a step: the caller's split count, or the rule above.  Both
-// phases of a split step derive it from the same arguments.
-PartPlan make_plan(int64_t n_tgt_rows, int64_t n_drf_rows, int64_t nvec, int32_t override_splits, Dtype dt) {
+// phases of a split step derive it from the same arguments.  head_beside: the head's tiles may
+// run beside the reduction; they hold some of the device's places throughout, so that whole
+// rows would end in an uneven last round (256 x K=7, 4096 -> 256: 195.1 us in whole rows, 192
+// in two pieces, 190.6 in four).
+PartPlan make_plan(int64_t n_tgt_rows, int64_t n_drf_rows, int64_t nvec, int32_t override_splits, Dtype dt,
+                   bool head_beside) {
     PartPlan p{};
     p.n_tgt_rows = n_tgt_rows;
-    p.splits = override_splits > 0 ? override_splits : auto_splits(n_tgt_rows + n_drf_rows, nvec, reduce_slots(dt));
+    const int64_t rows = n_tgt_rows + n_drf_rows;
+    p.splits = override_splits > 0 ? override_splits : auto_splits(rows, nvec, reduce_slots(dt));
+    if (override_splits == 0 && head_beside && p.splits == 1 && rows <= kMaxReduceSlots &&
+        nvec >= 4 * 4 * kReduceThreads)
+        p.splits = 4;
     return p;
 }
 
@@ -226,7 +257,8 @@ cospec_status run(const Common &c, Phase phase, int32_t *accept_len, int32_t *ou
     }
     const Layout L = layout(rows, c.B, c.RT, c.D, c.head, c.V);
     const float *uniform = c.opts ? c.opts->sample_uniform : nullptr;
-    const PartPlan plan = make_plan(n_tgt, n_drf, nvec, override_splits, static_cast<Dtype>(c.dt));
+    const bool head_beside = !c.is_tree && c.D > 0 && head_tile_groups(static_cast<int64_t>(c.B) * c.D, c.head) > 0;
+    const PartPlan plan = make_plan(n_tgt, n_drf, nvec, override_splits, static_cast<Dtype>(c.dt), head_beside);
     if (uniform && !aligned(uniform, 4)) return COSPEC_ERR_INVALID_ARG;
     const float *policy_u = c.opts ? c.opts->policy_uniform : nullptr;
     if (policy_u && !aligned(policy_u, 4)) return COSPEC_ERR_INVALID_ARG;
@@ -280,7 +312,9 @@ cospec_status run(const Common &c, Phase phase, int32_t *accept_len, int32_t *ou
     // the reduction's launch for a whole step and on its own in the second phase of a
     // split one, instead of on the mismatch rows after the reduction (both forms of the
     // step then compute z alike)
-    const bool every_slot = fuse_head && phase != kReducePhase && m_cap <= kEverySlotMax;
+    const int32_t tile_groups = fuse_head ? head_tile_groups(m_cap, c.head) : 0;
+    const bool tiles = tile_groups > 0 && phase != kReducePhase;
+    const bool every_slot = fuse_head && phase != kReducePhase && (tiles || m_cap <= kEverySlotMax);
     HeadArgs ha{};
     if (head) {
         // no hidden rows at all (a packed array of none): every z is NaN, and the GEMMs'
@@ -297,6 +331,14 @@ cospec_status run(const Common &c, Phase phase, int32_t *accept_len, int32_t *ou
         ha.d = c.head->d; ha.h = c.head->h;
         ha.ksplit = ksplit_for(m_cap, c.head);
         if (every_slot && ha.ksplit > kEverySlotSplits) ha.ksplit = kEverySlotSplits;
+        if (tiles) {
+            // beside the reduction a workgroup sums a whole group of slices; on its own, one
+            // slice, and the second layer sums the groups
+            const int32_t per = kHeadTileSlices / tile_groups;
+            ha.ksplit = phase == kWhole ? tile_groups : kHeadTileSlices;
+            ha.kgroup = phase == kWhole ? per : 1;
+            ha.zgroup = phase == kWhole ? 1 : per;
+        }
         // Trees mismatch most of their slots (about 60% on the 64-tree batch: 304
         // workgroups at 8 k-slices), more than one workgroup per CU: the shallow ring
         // lets two share a CU and finish in one round (19.9 -> 13.8 us there).
@@ -367,7 +409,7 @@ cospec_status run(const Common &c, Phase phase, int32_t *accept_len, int32_t *ou
         }
 
         if (!record(c.opts ? c.opts->reduce_begin : nullptr)) return COSPEC_ERR_HIP;
-        const hipError_t re = every_slot ? launch_reduce_head(dt, static_cast<Dtype>(c.head->dtype), ra, ha, c.stream)
+        const hipError_t re = tiles ? launch_reduce_tiles(dt, ra, ha, c.stream) : every_slot ? launch_reduce_head(dt, static_cast<Dtype>(c.head->dtype), ra, ha, c.stream)
                                          : launch_reduce(dt, ra, c.stream);
         if (re != hipSuccess) return COSPEC_ERR_HIP;
         if (!record(c.opts ? c.opts->reduce_end : nullptr)) return COSPEC_ERR_HIP;
@@ -403,7 +445,8 @@ cospec_status run(const Common &c, Phase phase, int32_t *accept_len, int32_t *ou
     if (!do_arbitrate) return COSPEC_OK;
     if (head && !(every_slot && do_reduce)) {
         const Dtype hdt = static_cast<Dtype>(c.head->dtype);
-        const hipError_t he = every_slot ? launch_slot_gemm(hdt, ha, c.stream)
+        const hipError_t he = tiles ? launch_tile_gemm(ha, c.stream)
+                              : every_slot ? launch_slot_gemm(hdt, ha, c.stream)
                               : fuse_head ? launch_head_gemm(hdt, ha, c.stream)
                                           : launch_head(hdt, ha, nullptr, c.stream);
         if (he != hipSuccess) return COSPEC_ERR_HIP;
@@ -659,7 +702,7 @@ cospec_status cospec_verify_block_sps(const void *target_logits, const void *dra
         override_splits = opts->splits;
     }
     const Layout L = layout(rows, B, K + 1, K, nullptr, V);
-    const PartPlan plan = make_plan(n_tgt, n_drf, nvec, override_splits, static_cast<Dtype>(logit_dtype));
+    const PartPlan plan = make_plan(n_tgt, n_drf, nvec, override_splits, static_cast<Dtype>(logit_dtype), false);
     if (rows * plan.splits > L.partial_slots || rows * plan.splits > INT32_MAX) return COSPEC_ERR_UNSUPPORTED;
     if (!workspace || !aligned(workspace, kAlign) || workspace_bytes < L.total) return COSPEC_ERR_WORKSPACE;
     char *ws = static_cast<char *>(workspace);

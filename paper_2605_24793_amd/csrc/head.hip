@@ -33,6 +33,7 @@
 #include "mfma.h"
 #include "rowstat.h"
 #include "slot_gemm.h"
+#include "tile_gemm.h"
 
 namespace cospec {
 namespace {
@@ -515,6 +516,13 @@ __global__ __launch_bounds__(kReduceThreads) void k_slot_gemm(HeadArgs a) {
     slotgemm::run<DT>(a, blockIdx.x, reinterpret_cast<const u32x4 *>(kZeroVec));
 }
 
+// The tiles of tile_gemm.h on their own, one slice of d per workgroup: the same sums as in the
+// whole step's reduction launch.
+__global__ __launch_bounds__(kReduceThreads) void k_tile_gemm(HeadArgs a) {
+    __shared__ __attribute__((aligned(16))) char s_ring[tilegemm::lds_bytes(tilegemm::kAlone)];
+    tilegemm::run<tilegemm::kAlone>(a, blockIdx.x, s_ring, reinterpret_cast<const u32x4 *>(kZeroVec));
+}
+
 // z[m] = w2 . relu(sum_ks upart[ks][m] + b1) + b2, one wave per row, fixed order.  ARB
 // (cospec_arbitrate): z goes to the caller with its threshold decision; an index outside
 // [0, n_rows) has z = NaN and accept 0.
@@ -523,7 +531,7 @@ __global__ __launch_bounds__(256) void k_head_epilogue(HeadArgs a, ArbOut o) {
     const int64_t M = a.count_dev ? static_cast<int64_t>(*a.count_dev) : a.count_host;
     const int64_t m = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (m >= M) return;
-    const float z = headz::head_z<DT, true>(a, m, threadIdx.x & 63, a.ksplit);
+    const float z = headz::head_z<DT, headz::kFew>(a, m, threadIdx.x & 63, a.ksplit);
     if ((threadIdx.x & 63) != 0) return;
     if constexpr (ARB) {
         if (o.z) o.z[m] = z;
@@ -590,6 +598,14 @@ hipError_t launch_slot_gemm(Dtype dt, const HeadArgs &a, hipStream_t s) {
     const dim3 grid(static_cast<unsigned>(blocks));
     if (dt == kBF16) hipLaunchKernelGGL(k_slot_gemm<kBF16>, grid, dim3(kReduceThreads), 0, s, a);
     else hipLaunchKernelGGL(k_slot_gemm<kF32>, grid, dim3(kReduceThreads), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_tile_gemm(const HeadArgs &a, hipStream_t s) {
+    if (a.m_cap <= 0 || a.m_cap > slotgemm::kMaxSlots || a.ksplit * a.kgroup != kHeadTileSlices) return hipErrorInvalidValue;
+    const int64_t blocks = tilegemm::blocks(a);
+    if (blocks > INT32_MAX) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_tile_gemm, dim3(static_cast<unsigned>(blocks)), dim3(kReduceThreads), 0, s, a);
     return hipGetLastError();
 }
 

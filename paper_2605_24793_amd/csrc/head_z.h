@@ -51,7 +51,7 @@ __device__ inline int live_ksplit(const HeadArgs &a, int64_t M) {
 // dropped), b1 and w2 included, so that none waits for another.  The partials are read
 // once: nontemporal loads keep them from displacing W1 in L2, which the next step's GEMM
 // reads again (measured: the large chain batch's GEMM 15.7 -> 13.8 us).
-template <int DT, int CPL, int SPL>
+template <int DT, int CPL, int SPL, bool GROUPS>
 __device__ inline float head_z_cols(const HeadArgs &a, int64_t m, int lane, int ksplit) {
     const void *b1 = a.b1 ? a.b1 : a.w2;                  // no bias: read w2, use 0
     float acc = 0.f;
@@ -74,10 +74,22 @@ __device__ inline float head_z_cols(const HeadArgs &a, int64_t m, int lane, int 
                     const int kc = min(k0 + k, ksplit - 1);
                     u[i][k] = __builtin_nontemporal_load(&a.upart[(static_cast<int64_t>(kc) * a.m_cap + m) * a.h + nc]);
                 }
+            if constexpr (GROUPS) {   // groups of slices first (at most kHeadTileSlices slices, whole groups)
 #pragma unroll
-            for (int i = 0; i < CPL; ++i)
+                for (int i = 0; i < CPL; ++i) {
+                    float g = 0.f;
 #pragma unroll
-                for (int k = 0; k < SPL; ++k) v[i] += k0 + k < ksplit ? u[i][k] : 0.f;
+                    for (int k = 0; k < (SPL < kHeadTileSlices ? SPL : kHeadTileSlices); ++k) {
+                        g += u[i][k];
+                        if (((k + 1) & (a.zgroup - 1)) == 0) { v[i] += g; g = 0.f; }
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < CPL; ++i)
+#pragma unroll
+                    for (int k = 0; k < SPL; ++k) v[i] += k0 + k < ksplit ? u[i][k] : 0.f;
+            }
         }
 #pragma unroll
         for (int i = 0; i < CPL; ++i) {
@@ -94,14 +106,21 @@ __device__ inline float head_z_cols(const HeadArgs &a, int64_t m, int lane, int 
 
 // z of list entry m, in every lane of the calling wave, from the first `ksplit`
 // k-slices of upart; NaN when its hidden row is outside [0, n_rows).  Each column's
-// k-slices are summed in slice order.  FEW: also has the form for at most four slices (the
-// chain finish goes without: its slices are rarely so few, and the extra code cost the
-// 8 x K=5 step 0.3 us).
-template <int DT, bool FEW>
+// k-slices are summed in slice order (kGroups: in groups of a.zgroup of them, then the
+// groups).  kFew also has the form for at most four slices.  The forms are apart because
+// the chain finish is sensitive to its size: with all of them in one kernel the 8 x K=5
+// step took 15.4 us, with the plain one 14.6.
+enum ZForm { kPlain, kFew, kGroups };
+template <int DT, ZForm FORM>
 __device__ inline float head_z(const HeadArgs &a, int64_t m, int lane, int ksplit) {
+    constexpr bool G = FORM == kGroups;
     float acc;
-    if (FEW && ksplit <= 4) acc = a.h <= 256 ? head_z_cols<DT, 4, 4>(a, m, lane, ksplit) : head_z_cols<DT, 8, 4>(a, m, lane, ksplit);
-    else acc = a.h <= 256 ? head_z_cols<DT, 4, 16>(a, m, lane, ksplit) : head_z_cols<DT, 8, 8>(a, m, lane, ksplit);
+    if (FORM == kFew && ksplit <= 4)
+        acc = a.h <= 256 ? head_z_cols<DT, 4, 4, false>(a, m, lane, ksplit) : head_z_cols<DT, 8, 4, false>(a, m, lane, ksplit);
+    else if (G)   // eight slices
+        acc = a.h <= 256 ? head_z_cols<DT, 4, 8, G>(a, m, lane, ksplit) : head_z_cols<DT, 8, 8, G>(a, m, lane, ksplit);
+    else
+        acc = a.h <= 256 ? head_z_cols<DT, 4, 16, G>(a, m, lane, ksplit) : head_z_cols<DT, 8, 8, G>(a, m, lane, ksplit);
     const int64_t id = hidden_row(a, m);
     return id >= 0 && id < a.n_rows ? acc + a.b2 : NAN;
 }

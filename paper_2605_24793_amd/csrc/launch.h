@@ -17,6 +17,8 @@ constexpr int kHeadTileN = 128;       //                            columns of W
 constexpr int kHeadTargetBlocks = 128;
 constexpr int kHeadMaxSplit = 32;
 constexpr int kHeadMostBlocks = 512;  // slices are taken off while the grid exceeds two workgroups per CU
+constexpr int kHeadSmallTile = 64;    // the tiles of the first layer beside the reduction
+constexpr int kHeadTileSlices = 8;    // ... and the slices of d they sum by themselves
 constexpr int kXcds = 8;             // MI355X: 8 XCDs, each with its own L2
 constexpr int kMaxSeqRows = 256;      // rows per sequence / nodes per tree held in LDS
 constexpr int kSegVecs = 64;          // 16-byte vectors per probability-mass segment (one wave load)
@@ -130,6 +132,10 @@ struct HeadArgs {
     int32_t d, h;
     int32_t ksplit;            // slices of d, one workgroup each (head_ksplit); the
                                // persistent form may use fewer (headz::live_ksplit)
+    // The first layer in tiles beside the reduction (tile_gemm.h; else 0, 0): the
+    // kHeadTileSlices slices of d that one workgroup sums, and how many consecutive stored
+    // slices the second layer sums before it adds them up (powers of two).
+    int32_t kgroup, zgroup;
     int32_t grid;              // chains: workgroups of the persistent GEMM (at most one per
                                // resident slot); 0: one workgroup per (tile, k-slice)
     int32_t two_per_cu;        // use the shallow LDS ring: two workgroups fit on a CU
@@ -273,6 +279,9 @@ hipError_t launch_reduce(Dtype dt, const ReduceArgs &a, hipStream_t s);
 // The reduction with the head's first layer over all h.m_cap decision slots in the same
 // launch (chains; h.upart by slot, h.ksplit slices; logit dtype dt, head dtype hdt).
 hipError_t launch_reduce_head(Dtype dt, Dtype hdt, const ReduceArgs &a, const HeadArgs &h, hipStream_t s);
+// The same with the first layer in tiles (bf16 heads), and the tiles on their own.
+hipError_t launch_reduce_tiles(Dtype dt, const ReduceArgs &a, const HeadArgs &h, hipStream_t s);
+hipError_t launch_tile_gemm(const HeadArgs &a, hipStream_t s);
 int32_t reduce_slots(Dtype dt);   // reduction workgroups resident at once on the current device
 hipError_t launch_sample(Dtype dt, const SampleArgs &a, hipStream_t s);
 hipError_t launch_decide(Dtype dt, const DecideArgs &a, hipStream_t s);

@@ -33,6 +33,7 @@
 #include "launch.h"
 #include "rowstat.h"
 #include "slot_gemm.h"
+#include "tile_gemm.h"
 
 // Products and sums are rounded as written in this file: the references (x * log2e
 // rounded) must be the same numbers in every kernel that forms them, so no
@@ -632,6 +633,20 @@ void k_vocab_reduce_head(ReduceArgs a, HeadArgs h, int head_blocks) {
     reduce_unit<DT, SEG>(a, blockIdx.x - head_blocks);
 }
 
+// A chain step's reduction launch with the head's first layer in tiles beside it
+// (tile_gemm.h): the first `head_blocks` workgroups take the tiles, the rest the reduction's
+// units.  The occupancy bound is k_vocab_reduce's own, as above.
+template <int DT, bool SEG>
+__global__ __launch_bounds__(kReduceThreads) __attribute__((amdgpu_waves_per_eu(DT == kBF16 && !SEG ? 8 : 6)))
+void k_vocab_reduce_tiles(ReduceArgs a, HeadArgs h, int head_blocks) {
+    __shared__ __attribute__((aligned(16))) char s_ring[tilegemm::lds_bytes(tilegemm::kBeside)];
+    if (static_cast<int>(blockIdx.x) < head_blocks) {
+        tilegemm::run<tilegemm::kBeside>(h, blockIdx.x, s_ring, &kZero16);
+        return;
+    }
+    reduce_unit<DT, SEG>(a, blockIdx.x - head_blocks);
+}
+
 template <int DT>
 __global__ __launch_bounds__(kDecideThreads) void k_decide(DecideArgs a) {
     decide_seq<DT>(a, blockIdx.x);
@@ -705,6 +720,24 @@ hipError_t launch_reduce_head(Dtype dt, Dtype hdt, const ReduceArgs &a, const He
     } else {
         if (a.seg) launch_reduce_head_t<kF32, true>(hdt, a, h, hbi, grid, s);
         else launch_reduce_head_t<kF32, false>(hdt, a, h, hbi, grid, s);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_reduce_tiles(Dtype dt, const ReduceArgs &a, const HeadArgs &h, hipStream_t s) {
+    if (h.m_cap <= 0 || h.m_cap > slotgemm::kMaxSlots || h.ksplit < 1 || h.ksplit * h.kgroup != kHeadTileSlices)
+        return hipErrorInvalidValue;
+    const int64_t hb = tilegemm::blocks(h);
+    const int64_t units = static_cast<int64_t>(a.n_rows) * a.plan.splits;
+    if (hb + units > INT32_MAX) return hipErrorInvalidValue;
+    const dim3 grid(static_cast<unsigned>(hb + units)), block(kReduceThreads);
+    const int hbi = static_cast<int>(hb);
+    if (dt == kBF16) {
+        if (a.seg) hipLaunchKernelGGL((k_vocab_reduce_tiles<kBF16, true>), grid, block, 0, s, a, h, hbi);
+        else hipLaunchKernelGGL((k_vocab_reduce_tiles<kBF16, false>), grid, block, 0, s, a, h, hbi);
+    } else {
+        if (a.seg) hipLaunchKernelGGL((k_vocab_reduce_tiles<kF32, true>), grid, block, 0, s, a, h, hbi);
+        else hipLaunchKernelGGL((k_vocab_reduce_tiles<kF32, false>), grid, block, 0, s, a, h, hbi);
     }
     return hipGetLastError();
 }

@@ -242,7 +242,7 @@ __global__ __launch_bounds__(256) void k_chain_finish(FinishArgs a) {
 // K = 15 10.9 -> 9.2 us, 48 of K = 25 17.5 -> 12.9 us.  Blocks of K <= 7 keep a kernel
 // compiled for eight waves: in the other, 8 x K=5 steps took 15.1 us instead of 14.6.
 constexpr int kFinishWaves = 12, kFinishWavesShort = 8;
-template <int HD, int PM, int WAVES>
+template <int HD, int PM, int WAVES, headz::ZForm FORM>
 __global__ __launch_bounds__(64 * WAVES) void k_chain_finish_head(FinishArgs a) {
     __shared__ float s_z[64];                              // K <= 64
     const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_chain_finish_head(FinishArgs a) 
         // the first layer ran on every slot: z of every slot, waiting for nothing (wave 0
         // uses the mismatches' only)
         for (int t = wave - 1; t < K; t += waves - 1) {    // wave-uniform
-            const float z = headz::head_z<HD, false>(a.hd, static_cast<int64_t>(b) * K + t, lane, a.hd.ksplit);
+            const float z = headz::head_z<HD, FORM>(a.hd, static_cast<int64_t>(b) * K + t, lane, a.hd.ksplit);
             if (lane == 0) s_z[t] = z;
         }
     } else {
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_chain_finish_head(FinishArgs a) 
         const int ksl = headz::live_ksplit(a.hd, M);
         for (uint64_t m = __ballot(need); m; m &= m - 1) {  // wave-uniform
             const int s = wave - 1 + __builtin_ctzll(m) * (waves - 1);
-            const float z = headz::head_z<HD, false>(a.hd, static_cast<int64_t>(b) * K + s, lane, ksl);
+            const float z = headz::head_z<HD, FORM>(a.hd, static_cast<int64_t>(b) * K + s, lane, ksl);
             if (lane == 0) s_z[s] = z;
         }
     }
@@ -413,17 +413,18 @@ __global__ __launch_bounds__(kMaxSeqRows) void k_tree_finish(FinishArgs a) {
     }
 }
 
-template <int WAVES>
-void launch_chain_finish_head(const FinishArgs &a, bool one, hipStream_t s) {
+template <int WAVES, headz::ZForm FORM, int HD>
+void launch_chain_finish_head(const FinishArgs &a, hipStream_t s) {
     const dim3 grid(a.B), block(64 * std::min(a.D + 1, WAVES));   // D >= 1 when the head ran
-    const bool bf = a.head_dt == kBF16;
-    if (one) {
-        if (bf) hipLaunchKernelGGL((k_chain_finish_head<kBF16, kPartOne, WAVES>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k_chain_finish_head<kF32, kPartOne, WAVES>), grid, block, 0, s, a);
-    } else {
-        if (bf) hipLaunchKernelGGL((k_chain_finish_head<kBF16, kPartSplit, WAVES>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k_chain_finish_head<kF32, kPartSplit, WAVES>), grid, block, 0, s, a);
-    }
+    if (a.plan.splits == 1) hipLaunchKernelGGL((k_chain_finish_head<HD, kPartOne, WAVES, FORM>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_chain_finish_head<HD, kPartSplit, WAVES, FORM>), grid, block, 0, s, a);
+}
+
+template <int WAVES>
+void launch_chain_finish_waves(const FinishArgs &a, hipStream_t s) {
+    if (a.head_dt != kBF16) launch_chain_finish_head<WAVES, headz::kPlain, kF32>(a, s);
+    else if (a.hd.zgroup > 1) launch_chain_finish_head<WAVES, headz::kGroups, kBF16>(a, s);
+    else launch_chain_finish_head<WAVES, headz::kPlain, kBF16>(a, s);
 }
 
 }  // namespace
@@ -436,8 +437,8 @@ hipError_t launch_finish(Dtype dt, const FinishArgs &a, hipStream_t s) {
     } else {
         const bool one = a.plan.splits == 1;
         if (a.fuse_head) {
-            if (a.D + 1 <= kFinishWavesShort) launch_chain_finish_head<kFinishWavesShort>(a, one, s);
-            else launch_chain_finish_head<kFinishWaves>(a, one, s);
+            if (a.D + 1 <= kFinishWavesShort) launch_chain_finish_waves<kFinishWavesShort>(a, s);
+            else launch_chain_finish_waves<kFinishWaves>(a, s);
         } else {
             const unsigned blocks = static_cast<unsigned>((a.B + 3) / 4);
             if (one) hipLaunchKernelGGL(k_chain_finish<kPartOne>, dim3(blocks), dim3(256), 0, s, a);

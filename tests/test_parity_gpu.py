@@ -1086,3 +1086,41 @@ def test_chain_finish_slots_per_wave(B, K, noise):
     assert B * K > 256
     gpu = _gpu_block(wl, 0.5)
     parity.check_block(gpu, _ref_block(wl, 0.5))
+
+
+@pytest.mark.parametrize("B,K,d,h,ldt,packed,t1", [
+    (7, 7, 512, 65, "bf16", False, False),      # 49 slots, one column past a tile, slices of one piece
+    (16, 4, 520, 64, "bf16", True, False),      # one whole tile; d past four slices, three slices empty
+    (13, 5, 456, 128, "f32", False, False),     # 65 slots, a last slice of eight elements, fp32 logits
+    (41, 25, 1024, 256, "bf16", False, True),   # 17 x 4 tiles in two groups, temperature 1
+    (40, 12, 640, 600, "bf16", True, True),     # 8 x 10 tiles, h past whole tiles
+    (60, 17, 512, 512, "bf16", False, False),   # 16 x 8 = 128 tiles, the most
+    (61, 17, 512, 512, "bf16", False, False),   # 17 x 8: past them, on the mismatch rows
+])
+def test_chain_head_tiles(B, K, d, h, ldt, packed, t1):
+    # the head's first layer in 64 x 64 tiles over every decision slot: against the oracle, and
+    # the two phases of a split step bit for bit the whole step
+    wl = workloads.make_chain(B=B, K=K, V=3001, d=d, h=h, dtype="bf16", seed=B + K, bias=True, noise=1.2)
+    if ldt == "f32":
+        wl.target, wl.draft = wl.target.float(), wl.draft.float()
+    g = torch.Generator().manual_seed(7)
+    u = torch.rand(B, K + 1, generator=g) if t1 else None
+    hid, row0 = wl.hidden, None
+    if packed:                                                  # two rows between sequences
+        hid = torch.zeros(B * (K + 2), d, dtype=wl.hidden.dtype)
+        row0 = torch.arange(B, dtype=torch.int64) * (K + 2) + 1
+        for b in range(B):
+            hid[b * (K + 2) + 1:b * (K + 2) + 1 + K] = wl.hidden[b]
+    tgt, drf, tok = _padded(wl.target, 7), _padded(wl.draft, 7), wl.draft_tokens.to(DEV)
+    ud = None if u is None else u.to(DEV)
+    r0 = None if row0 is None else row0.to(DEV)
+    whole = cs.verify_block(tgt, drf, tok, hid.to(DEV), _head_dev(wl.head), 0.4, sample_u=ud, hidden_row0=r0)
+    sb = cs.SplitBlock(tgt, drf, tok, _head_dev(wl.head), sample_u=ud)
+    split = sb.arbitrate(hid.to(DEV), 0.4, hidden_row0=r0)
+    torch.cuda.synchronize()
+    for k, v in whole.items():
+        assert torch.equal(v.view(torch.int32) if v.dtype == torch.float32 else v,
+                           split[k].view(torch.int32) if v.dtype == torch.float32 else split[k]), k
+    gpu = {k: v.cpu() for k, v in whole.items()}
+    cand = gpu["tgt_candidate"].numpy() if t1 else None
+    parity.check_block(gpu, _ref_block(wl, 0.4, u, cand))
