@@ -720,7 +720,9 @@ cospec_status cospec_verify_block_sps(const void *target_logits, const void *dra
     ra.plan = plan;
     ra.vec_per_split = static_cast<int32_t>(split_vectors(nvec, plan.splits, false));
     ra.partials = partials;
-    ra.reset_counter = reinterpret_cast<int32_t *>(ws + L.count);
+    ra.chain_tokens = draft_tokens;
+    ra.K = K;
+    ra.xtok = reinterpret_cast<float *>(ws + L.xtok);
     if (opts && opts->reduce_begin && hipEventRecord(opts->reduce_begin, stream) != hipSuccess) return COSPEC_ERR_HIP;
     if (launch_reduce(dt, ra, stream) != hipSuccess) return COSPEC_ERR_HIP;
     if (opts && opts->reduce_end && hipEventRecord(opts->reduce_end, stream) != hipSuccess) return COSPEC_ERR_HIP;
@@ -729,23 +731,12 @@ cospec_status cospec_verify_block_sps(const void *target_logits, const void *dra
         return COSPEC_ERR_HIP;
     if (opts && opts->reduce2_end && hipEventRecord(opts->reduce2_end, stream) != hipSuccess) return COSPEC_ERR_HIP;
 
-    DecideArgs da{};
-    da.tgt = ra.tgt; da.ld_bytes = ra.ld_bytes; da.V = V; da.B = B; da.RT = K + 1; da.D = K;
-    da.tokens = draft_tokens; da.partials = partials; da.plan = plan;
-    da.tgt_argmax = F.tgt_argmax; da.tgt_max = F.tgt_max; da.tgt_lse = F.tgt_lse; da.tgt_ent = F.tgt_entropy;
-    da.tgt_cand = F.tgt_candidate; da.logp_tgt = F.logp_tgt; da.delta = F.delta;
-    da.ws_tgt_arg = reinterpret_cast<int32_t *>(ws + L.tgt_arg);
-    da.ws_logp_tgt = reinterpret_cast<float *>(ws + L.logp);
-    da.ws_state = reinterpret_cast<uint8_t *>(ws + L.state);
-    da.ws_listpos = reinterpret_cast<int32_t *>(ws + L.listpos);
-    da.ws_list = reinterpret_cast<int32_t *>(ws + L.list);
-    da.ws_count = reinterpret_cast<int32_t *>(ws + L.count);
-    if (launch_decide(dt, da, stream) != hipSuccess) return COSPEC_ERR_HIP;
-
     SpsArgs sa{};
     sa.tgt = ra.tgt; sa.drf = ra.drf; sa.ld_bytes = ra.ld_bytes; sa.V = V; sa.B = B; sa.K = K;
     sa.tokens = draft_tokens; sa.uniform = uniforms; sa.partials = partials; sa.plan = plan;
-    sa.ws_state = da.ws_state; sa.ws_logp_tgt = da.ws_logp_tgt;
+    sa.ws_xtok = ra.xtok;
+    sa.tgt_argmax = F.tgt_argmax; sa.tgt_max = F.tgt_max; sa.tgt_lse = F.tgt_lse; sa.tgt_ent = F.tgt_entropy;
+    sa.tgt_cand = F.tgt_candidate; sa.logp_tgt = F.logp_tgt; sa.delta = F.delta;
     sa.seg_mass = reinterpret_cast<float *>(ws + L.seg);
     sa.nseg = static_cast<int32_t>(n_segments(V, eb));
     sa.accept_len = accept_len; sa.out_tokens = out_tokens;

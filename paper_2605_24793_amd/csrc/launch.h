@@ -217,8 +217,9 @@ struct SpsArgs {
     const float *uniform;      // [B][K+1]: K acceptance tests, then the last token's draw
     const float4 *partials;
     PartPlan plan;             // draft row j is row B * (K+1) + j
-    const uint8_t *ws_state;   // decide's state (invalid tokens are rejected)
-    const float *ws_logp_tgt;
+    const float *ws_xtok;      // the logit at each row's token (ReduceArgs::xtok)
+    int32_t *tgt_argmax; float *tgt_max; float *tgt_lse; float *tgt_ent; int32_t *tgt_cand;
+    float *logp_tgt; uint8_t *delta;
     float *seg_mass;           // [B][nseg] weights of the last token's distribution
     int32_t nseg;
     int32_t *accept_len; int32_t *out_tokens;

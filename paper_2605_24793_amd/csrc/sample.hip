@@ -21,6 +21,7 @@
 namespace cospec {
 namespace {
 
+constexpr int kRun = 8;                       // segment masses of a lane read at once
 constexpr float kBelowOne = 0x1.fffffep-1f;   // largest float below 1
 
 __device__ inline float wave_incl_scan(float x, int lane) {
@@ -42,18 +43,28 @@ __global__ __launch_bounds__(256) void k_sample(SampleArgs a) {
     const int lane = threadIdx.x & 63;
     const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= a.n_rows) return;                                   // whole wave leaves
-    const RowParts parts = row_parts(a.plan, row);
-    const RowStat rs = merge_row(a.partials + parts.first, parts.count);
-    const float R = __fmul_rn(rs.max, kLog2e);
-    float u = a.uniform[row];
-    u = u >= 0.f ? fminf(u, kBelowOne) : 0.f;                      // NaN and negatives act as 0
-
-    // 1. the segment where the cumulative mass crosses u * total
+    // every load that waits for no other goes out first: the uniform, the partials and the
+    // first kRun masses of this lane's run of segments (all of it up to 512 segments a row)
     const float2 *sg = a.seg + static_cast<int64_t>(row) * a.nseg;
     const int per = (a.nseg + 63) / 64;
     const int s0 = min(lane * per, a.nseg), s1 = min(s0 + per, a.nseg);
+    float u = a.uniform[row];
+    float2 v[kRun];
+#pragma unroll
+    for (int i = 0; i < kRun; ++i) v[i] = sg[min(s0 + i, a.nseg - 1)];   // unconditional: clamped
+    const RowParts parts = row_parts(a.plan, row);
+    const RowStat rs = merge_row(a.partials + parts.first, parts.count);
+    const float R = __fmul_rn(rs.max, kLog2e);
+    u = u >= 0.f ? fminf(u, kBelowOne) : 0.f;                      // NaN and negatives act as 0
+
+    // 1. the segment where the cumulative mass crosses u * total
     float run = 0.f;
-    for (int s = s0; s < s1; ++s) run += seg_mass(sg[s], R);
+#pragma unroll
+    for (int i = 0; i < kRun; ++i) {
+        const float m = seg_mass(v[i], R);
+        run += s0 + i < s1 ? m : 0.f;
+    }
+    for (int s = s0 + kRun; s < s1; ++s) run += seg_mass(sg[s], R);
     const float incl = wave_incl_scan(run, lane);
     const float up = __shfl_up(incl, 1);
     const float excl = lane ? up : 0.f;
@@ -73,15 +84,20 @@ __global__ __launch_bounds__(256) void k_sample(SampleArgs a) {
     if (lane == L) {
         float cum = excl, cum_last = excl;
         int last = -1;
-        for (int s = s0; s < s1; ++s) {
-            const float m = seg_mass(sg[s], R);
+        auto step = [&](int s, float m) {                          // true once the crossing is found
             if (m > 0.f) {
                 last = s;
                 cum_last = cum;
-                if (cum + m > target) { segsel = s; before = cum; break; }
+                if (cum + m > target) { segsel = s; before = cum; return true; }
             }
             cum += m;
-        }
+            return false;
+        };
+        bool found = false;
+#pragma unroll
+        for (int i = 0; i < kRun; ++i)
+            if (!found && s0 + i < s1) found = step(s0 + i, seg_mass(v[i], R));
+        for (int s = s0 + kRun; !found && s < s1; ++s) found = step(s, seg_mass(sg[s], R));
         if (segsel < 0) { segsel = last; before = cum_last; }
     }
     segsel = max(__shfl(segsel, L), 0);        // -1 only if no segment had mass at all
