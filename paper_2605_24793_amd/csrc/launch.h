@@ -113,6 +113,14 @@ struct SampleArgs {
     int32_t nseg;
     const float *uniform;      // [n_rows]
     int32_t *cand;             // [n_rows] out
+    // Chains, first phase of a split step (tokens not null): the decision step's outputs, which
+    // for a chain are each row's own: the row's statistics, and for rows i < K Delta and
+    // log p_T of draft token i + 1 from the logit the reduction stored.
+    const int32_t *tokens;     // [B][K]
+    const float *xtok;
+    int32_t K;
+    int32_t *tgt_argmax; float *tgt_max; float *tgt_lse; float *tgt_ent; int32_t *tgt_cand;
+    float *logp_tgt; uint8_t *delta;
 };
 
 

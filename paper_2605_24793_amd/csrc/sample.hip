@@ -52,6 +52,13 @@ __global__ __launch_bounds__(256) void k_sample(SampleArgs a) {
     float2 v[kRun];
 #pragma unroll
     for (int i = 0; i < kRun; ++i) v[i] = sg[min(s0 + i, a.nseg - 1)];   // unconditional: clamped
+    const int sb = a.tokens ? row / (a.K + 1) : 0, si = row - sb * (a.K + 1);   // chain and row in it
+    int tok = -1;
+    float xt = 0.f;
+    if (a.tokens && si < a.K) {
+        tok = a.tokens[static_cast<int64_t>(sb) * a.K + si];
+        xt = a.xtok[row];
+    }
     const RowParts parts = row_parts(a.plan, row);
     const RowStat rs = merge_row(a.partials + parts.first, parts.count);
     const float R = __fmul_rn(rs.max, kLog2e);
@@ -147,7 +154,20 @@ __global__ __launch_bounds__(256) void k_sample(SampleArgs a) {
     } else {                           // every element underflowed against the row max
         idx = __shfl(first, 0);
     }
-    if (lane == 0) a.cand[row] = idx;
+    if (lane != 0) return;
+    a.cand[row] = idx;
+    if (!a.tokens) return;
+    if (a.tgt_cand) a.tgt_cand[row] = idx;
+    if (a.tgt_argmax) a.tgt_argmax[row] = rs.arg;
+    if (a.tgt_max) a.tgt_max[row] = rs.max;
+    if (a.tgt_lse) a.tgt_lse[row] = rs.lse;
+    if (a.tgt_ent) a.tgt_ent[row] = rs.ent;
+    if (si < a.K) {
+        const int64_t di = static_cast<int64_t>(sb) * a.K + si;
+        const bool valid = tok >= 0 && tok < a.V;
+        if (a.delta) a.delta[di] = valid && tok == idx;
+        if (a.logp_tgt) a.logp_tgt[di] = valid ? (xt - rs.max) - rs.log_s : NAN;
+    }
 }
 
 }  // namespace

@@ -1124,3 +1124,22 @@ def test_chain_head_tiles(B, K, d, h, ldt, packed, t1):
     gpu = {k: v.cpu() for k, v in whole.items()}
     cand = gpu["tgt_candidate"].numpy() if t1 else None
     parity.check_block(gpu, _ref_block(wl, 0.4, u, cand))
+
+
+@pytest.mark.parametrize("B,K,V", [(3, 1, 4097), (5, 7, 20001), (2, 64, 513)])
+def test_split_t1_first_phase_outputs(B, K, V):
+    # at temperature 1 the first phase's sampling also writes the decision step's outputs: bit
+    # for bit those of the whole step, an invalid draft token included
+    wl = workloads.make_chain(B=B, K=K, V=V, d=64, h=32, dtype="bf16", seed=V, noise=0.5)
+    tok = wl.draft_tokens.clone()
+    tok[0, 0], tok[-1, -1] = -1, V
+    u = _uniforms((B, K + 1), 17).to(DEV)
+    tgt, drf = wl.target.to(DEV), wl.draft.to(DEV)
+    if V % 8:
+        tgt, drf = _padded(wl.target, 3), _padded(wl.draft, 3)
+    whole = cs.verify_block(tgt, drf, tok.to(DEV), wl.hidden.to(DEV), _head_dev(wl.head), 0.5, sample_u=u)
+    sb = cs.SplitBlock(tgt, drf, tok.to(DEV), _head_dev(wl.head), sample_u=u)
+    torch.cuda.synchronize()
+    first = dict(sb.features, tgt_candidate=sb.candidates)
+    _same(whole, first, ["tgt_argmax", "tgt_max", "tgt_lse", "tgt_entropy", "tgt_candidate", "delta", "logp_tgt"])
+    assert not first["delta"][0, 0] and torch.isnan(first["logp_tgt"][-1, -1])
