@@ -26,9 +26,6 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 # Chain batches of at most this many decision slots run the head's first layer in the
 # reduction's launch (kEverySlotMax in paper_2605_24793_amd/csrc/cospec_api.hip).
 EVERY_SLOT_MAX = 256
-# ... and with a bf16 head, from this many slots (kTilesMinSlots there) and up to this many
-# tiles of 64 slots x 64 columns, in tiles in that launch.
-TILES_MIN_SLOTS, TILES_MAX = 49, 128
 sys.path.insert(0, ROOT)
 
 METRIC = "verified rows/sec (B×(k+1)) and achieved HBM GB/s vs peak, V=151936 bf16"
@@ -226,6 +223,15 @@ def _conv(torch, bf16_bits, t):
     return bf16_bits(t) if t.dtype == torch.bfloat16 else t.contiguous().numpy()
 
 
+def head_in_tiles(slots, d, h, logit_bytes):
+    """Whether the library runs a bf16 head's first layer in tiles in the reduction's launch
+    (head_tile_groups in paper_2605_24793_amd/csrc/cospec_api.hip, to the label's needs)."""
+    tiles = -(-slots // 64) * -(-h // 64)
+    if slots < 49 or tiles > 256 or d < 449:
+        return False
+    return tiles <= 128 or d / 32 * 0.8 <= 0.5 * logit_bytes / 6.5e6
+
+
 class Step:
     """One workload resident on the GPU with its pre-marshalled verify call."""
 
@@ -262,9 +268,9 @@ class Step:
             # the library runs the head's first layer over every decision slot in the
             # reduction's launch: the timed launch holds both
             self.kernel = "k_vocab_reduce_head (reduction + the head's first layer on every slot)"
-        slots = 0 if self.tree or sps_u is not None else wl.B * wl.K
-        tiles = -(-slots // 64) * -(-wl.head.h // 64)
-        if slots >= TILES_MIN_SLOTS and tiles <= TILES_MAX and wl.head.w1.dtype == torch.bfloat16 and wl.head.d >= 449:
+        slots = wl.B * (wl.N if self.tree else wl.K)
+        if sps_u is None and wl.head.w1.dtype == torch.bfloat16 and head_in_tiles(
+                slots, wl.head.d, wl.head.h, self.rows * 2 * wl.V * self.elem):
             self.kernel = "k_vocab_reduce_tiles (reduction + the head's first layer in tiles)"
         self.logit_bytes = self.reduced_rows * wl.V * self.elem   # algorithmic bytes of the reductions
         self.step = self.p.launch

@@ -88,21 +88,30 @@ inline size_t head_bytes(int64_t m_cap, const cospec_head *hd) {
                     static_cast<size_t>(hd->h) * 4);
 }
 
-// Chain batches whose head's first layer runs in tiles over every decision slot, beside the
-// reduction (tile_gemm.h): the slice groups a tile's workgroups share out (1, 2, 4 or 8; 0: not
-// in tiles).  bf16 heads only.  As many groups as keep the tiles' workgroups at one per CU:
-// more displace the reduction, fewer end after it (64 x K=7, 28 tiles: 54.4 us with 4 groups,
-// 55.6 with 8, 61.8 with 2, 65.4 on the mismatch rows after the reduction; 48 x K=10, 5120 ->
-// 512, 64 tiles: 56.2 with 4, 61.1 with 8, 69.0 after; 128 x K=7, 5120 -> 512, 112 tiles: 104.3
-// with 2, 110.2 with 4, 115.8 after).  From 129 tiles on a group would be all of d, and the
-// tiles outlast the reduction (256 x K=7, 5120 -> 512, 224 tiles: 195 either way).
-int32_t head_tile_groups(int64_t m_cap, const cospec_head *hd) {
+// Steps whose head's first layer runs in tiles over every decision slot, beside the reduction
+// of `logit_bytes` (tile_gemm.h): the slice groups a tile's workgroups share out (1, 2, 4 or 8;
+// 0: not in tiles).  bf16 heads only.
+//  - As many groups as keep the tiles' workgroups at one per CU: more displace the reduction
+//    (64 x K=7, 28 tiles: 54.4 us with 4 groups, 55.6 with 8, 61.8 with 2, 65.4 on the mismatch
+//    rows after the reduction; 48 x K=10, 5120 -> 512, 64 tiles: 56.2 with 4, 61.1 with 8, 69.0
+//    after; 128 x K=7, 5120 -> 512, 112 tiles: 104.3 with 2, 110.2 with 4, 115.8 after).
+//  - More while they would outlast the reduction, at about 0.8 us a stage of 32 elements of
+//    d beside it against 6.5 TB/s (16 trees of 38 nodes, 5120 -> 512, 80 tiles, 245 MB: 68.3 with
+//    2 groups, 61.8 with 4, 67.2 after).
+//  - One group, all of d, only when it takes at most half of the reduction (64 trees of 60
+//    nodes, 4096 -> 256, 240 tiles: 294.5 us, 299.1 after; but 256 x K=7, 5120 -> 512, 224 tiles,
+//    195 either way), and up to one workgroup per CU.
+int32_t head_tile_groups(int64_t m_cap, const cospec_head *hd, int64_t logit_bytes) {
+    constexpr int64_t kCus = 256;
     if (hd->dtype != COSPEC_BF16 || m_cap < kTilesMinSlots) return 0;
     const int64_t tiles = (m_cap + kHeadSmallTile - 1) / kHeadSmallTile * ((hd->h + kHeadSmallTile - 1) / kHeadSmallTile);
     // the partials of the eight slices of the form on its own need their place
-    if (tiles > 128 || ksplit_for(m_cap, hd) < kHeadTileSlices) return 0;
+    if (tiles > kCus || ksplit_for(m_cap, hd) < kHeadTileSlices) return 0;
+    const double reduce_us = static_cast<double>(logit_bytes) / 6.5e6, tile_us = hd->d / 32 * 0.8;
     int32_t groups = kHeadTileSlices;
-    while (tiles * groups > 256) groups /= 2;
+    while (tiles * groups > kCus) groups /= 2;
+    if (groups == 1 && tile_us > 0.5 * reduce_us) return 0;
+    while (groups < kHeadTileSlices && tile_us > groups * reduce_us) groups *= 2;
     return groups;
 }
 
@@ -240,6 +249,11 @@ struct Common {
     hipStream_t stream;
 };
 
+// Logit bytes the step's reduction reads (trees: about half of the draft rows have a child).
+int64_t step_logit_bytes(const Common &c) {
+    return static_cast<int64_t>(c.B) * (c.RT + (c.is_tree ? c.RD / 2 : c.RD)) * c.V * elem_bytes(c.dt);
+}
+
 // Which part of the step a call enqueues: the whole step, or one of the two
 // phases of the split form (reductions + decide, then head + finish).
 enum Phase { kWhole, kReducePhase, kArbitratePhase };
@@ -257,7 +271,8 @@ cospec_status run(const Common &c, Phase phase, int32_t *accept_len, int32_t *ou
     }
     const Layout L = layout(rows, c.B, c.RT, c.D, c.head, c.V);
     const float *uniform = c.opts ? c.opts->sample_uniform : nullptr;
-    const bool head_beside = !c.is_tree && c.D > 0 && head_tile_groups(static_cast<int64_t>(c.B) * c.D, c.head) > 0;
+    const bool head_beside =
+        !c.is_tree && c.D > 0 && head_tile_groups(static_cast<int64_t>(c.B) * c.D, c.head, step_logit_bytes(c)) > 0;
     const PartPlan plan = make_plan(n_tgt, n_drf, nvec, override_splits, static_cast<Dtype>(c.dt), head_beside);
     if (uniform && !aligned(uniform, 4)) return COSPEC_ERR_INVALID_ARG;
     const float *policy_u = c.opts ? c.opts->policy_uniform : nullptr;
@@ -312,7 +327,7 @@ cospec_status run(const Common &c, Phase phase, int32_t *accept_len, int32_t *ou
     // the reduction's launch for a whole step and on its own in the second phase of a
     // split one, instead of on the mismatch rows after the reduction (both forms of the
     // step then compute z alike)
-    const int32_t tile_groups = fuse_head ? head_tile_groups(m_cap, c.head) : 0;
+    const int32_t tile_groups = head ? head_tile_groups(m_cap, c.head, step_logit_bytes(c)) : 0;
     const bool tiles = tile_groups > 0 && phase != kReducePhase;
     const bool every_slot = fuse_head && phase != kReducePhase && (tiles || m_cap <= kEverySlotMax);
     HeadArgs ha{};
@@ -339,6 +354,7 @@ cospec_status run(const Common &c, Phase phase, int32_t *accept_len, int32_t *ou
             ha.kgroup = phase == kWhole ? per : 1;
             ha.zgroup = phase == kWhole ? 1 : per;
         }
+        if (tiles && c.is_tree) ha.out_by_slot = 1;
         // Trees mismatch most of their slots (about 60% on the 64-tree batch: 304
         // workgroups at 8 k-slices), more than one workgroup per CU: the shallow ring
         // lets two share a CU and finish in one round (19.9 -> 13.8 us there).
@@ -453,7 +469,9 @@ cospec_status run(const Common &c, Phase phase, int32_t *accept_len, int32_t *ou
         }
     }
     if (!do_arbitrate) return COSPEC_OK;
-    if (head && !(every_slot && do_reduce)) {
+    if (head && c.is_tree && tiles) {
+        if (launch_head_epilogue(static_cast<Dtype>(c.head->dtype), ha, nullptr, c.stream) != hipSuccess) return COSPEC_ERR_HIP;
+    } else if (head && !(every_slot && do_reduce)) {
         const Dtype hdt = static_cast<Dtype>(c.head->dtype);
         const hipError_t he = tiles ? launch_tile_gemm(ha, c.stream)
                               : every_slot ? launch_slot_gemm(hdt, ha, c.stream)

@@ -523,7 +523,8 @@ __global__ __launch_bounds__(kReduceThreads) void k_tile_gemm(HeadArgs a) {
     tilegemm::run<tilegemm::kAlone>(a, blockIdx.x, s_ring, reinterpret_cast<const u32x4 *>(kZeroVec));
 }
 
-// z[m] = w2 . relu(sum_ks upart[ks][m] + b1) + b2, one wave per row, fixed order.  ARB
+// z[m] = w2 . relu(sum_ks upart[ks][m] + b1) + b2 of list entry m (out_by_slot: its partials
+// are at its decision slot, the entry itself), one wave per row, fixed order.  ARB
 // (cospec_arbitrate): z goes to the caller with its threshold decision; an index outside
 // [0, n_rows) has z = NaN and accept 0.
 template <int DT, bool ARB>
@@ -531,7 +532,8 @@ __global__ __launch_bounds__(256) void k_head_epilogue(HeadArgs a, ArbOut o) {
     const int64_t M = a.count_dev ? static_cast<int64_t>(*a.count_dev) : a.count_host;
     const int64_t m = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (m >= M) return;
-    const float z = headz::head_z<DT, headz::kFew>(a, m, threadIdx.x & 63, a.ksplit);
+    const int64_t e = a.list ? static_cast<int64_t>(a.list[m]) : m;
+    const float z = headz::head_z<DT, headz::kFew>(a, a.out_by_slot ? e : m, mapped_row(a, e), threadIdx.x & 63, a.ksplit);
     if ((threadIdx.x & 63) != 0) return;
     if constexpr (ARB) {
         if (o.z) o.z[m] = z;
@@ -641,10 +643,15 @@ hipError_t launch_head_gemm(Dtype dt, const HeadArgs &a, hipStream_t s) {
 }
 
 hipError_t launch_head(Dtype dt, const HeadArgs &a, const ArbOut *out, hipStream_t s) {
-    const dim3 egrid(static_cast<unsigned>((a.m_cap + 3) / 4)), block(256);
-    if (egrid.x == 0) return hipSuccess;
+    if (a.m_cap <= 0) return hipSuccess;
     const hipError_t e = launch_head_gemm(dt, a, s);
     if (e != hipSuccess) return e;
+    return launch_head_epilogue(dt, a, out, s);
+}
+
+hipError_t launch_head_epilogue(Dtype dt, const HeadArgs &a, const ArbOut *out, hipStream_t s) {
+    const dim3 egrid(static_cast<unsigned>((a.m_cap + 3) / 4)), block(256);
+    if (egrid.x == 0) return hipSuccess;
     const ArbOut o = out ? *out : ArbOut{};
     if (dt == kBF16) {
         if (out) hipLaunchKernelGGL((k_head_epilogue<kBF16, true>), egrid, block, 0, s, a, o);

@@ -28,11 +28,6 @@ __device__ inline int64_t mapped_row(const HeadArgs &a, int64_t id) {
     return id;
 }
 
-// Hidden row of list entry m.
-__device__ inline int64_t hidden_row(const HeadArgs &a, int64_t m) {
-    return mapped_row(a, a.list ? static_cast<int64_t>(a.list[m]) : m);
-}
-
 // k-slices the persistent GEMM cuts d into for M listed rows: a.ksplit while the
 // (tile, k-slice) items fit a.grid workgroups, else as many as fit (at least one).
 // The grid-sized form (a.grid = 0) always uses a.ksplit.
@@ -104,15 +99,15 @@ __device__ inline float head_z_cols(const HeadArgs &a, int64_t m, int lane, int 
     return acc;
 }
 
-// z of list entry m, in every lane of the calling wave, from the first `ksplit`
-// k-slices of upart; NaN when its hidden row is outside [0, n_rows).  Each column's
+// z of row m of upart, in every lane of the calling wave, from the first `ksplit` k-slices;
+// NaN when its hidden row id is outside [0, n_rows).  Each column's
 // k-slices are summed in slice order (kGroups: in groups of a.zgroup of them, then the
 // groups).  kFew also has the form for at most four slices.  The forms are apart because
 // the chain finish is sensitive to its size: with all of them in one kernel the 8 x K=5
 // step took 15.4 us, with the plain one 14.6.
 enum ZForm { kPlain, kFew, kGroups };
 template <int DT, ZForm FORM>
-__device__ inline float head_z(const HeadArgs &a, int64_t m, int lane, int ksplit) {
+__device__ inline float head_z(const HeadArgs &a, int64_t m, int64_t id, int lane, int ksplit) {
     constexpr bool G = FORM == kGroups;
     float acc;
     if (FORM == kFew && ksplit <= 4)
@@ -121,7 +116,6 @@ __device__ inline float head_z(const HeadArgs &a, int64_t m, int lane, int kspli
         acc = a.h <= 256 ? head_z_cols<DT, 4, 8, G>(a, m, lane, ksplit) : head_z_cols<DT, 8, 8, G>(a, m, lane, ksplit);
     else
         acc = a.h <= 256 ? head_z_cols<DT, 4, 16, G>(a, m, lane, ksplit) : head_z_cols<DT, 8, 8, G>(a, m, lane, ksplit);
-    const int64_t id = hidden_row(a, m);
     return id >= 0 && id < a.n_rows ? acc + a.b2 : NAN;
 }
 

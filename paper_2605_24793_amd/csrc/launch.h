@@ -297,6 +297,7 @@ hipError_t launch_decide(Dtype dt, const DecideArgs &a, hipStream_t s);
 int32_t head_ksplit(int64_t m_cap, int32_t d, int32_t h, int32_t elem_bytes);
 // GEMM + epilogue: z of the listed rows, or cospec_arbitrate's outputs when out is given.
 hipError_t launch_head(Dtype dt, const HeadArgs &a, const ArbOut *out, hipStream_t s);
+hipError_t launch_head_epilogue(Dtype dt, const HeadArgs &a, const ArbOut *out, hipStream_t s);
 hipError_t launch_head_gemm(Dtype dt, const HeadArgs &a, hipStream_t s);
 // The first layer over all a.m_cap decision slots on its own (slot_gemm.h).
 hipError_t launch_slot_gemm(Dtype dt, const HeadArgs &a, hipStream_t s);

@@ -255,7 +255,8 @@ __global__ __launch_bounds__(64 * WAVES) void k_chain_finish_head(FinishArgs a) 
         // the first layer ran on every slot: z of every slot, waiting for nothing (wave 0
         // uses the mismatches' only)
         for (int t = wave - 1; t < K; t += waves - 1) {    // wave-uniform
-            const float z = headz::head_z<HD, FORM>(a.hd, static_cast<int64_t>(b) * K + t, lane, a.hd.ksplit);
+            const int64_t di = static_cast<int64_t>(b) * K + t;
+            const float z = headz::head_z<HD, FORM>(a.hd, di, headz::mapped_row(a.hd, di), lane, a.hd.ksplit);
             if (lane == 0) s_z[t] = z;
         }
     } else {
@@ -277,7 +278,8 @@ __global__ __launch_bounds__(64 * WAVES) void k_chain_finish_head(FinishArgs a) 
         const int ksl = headz::live_ksplit(a.hd, M);
         for (uint64_t m = __ballot(need); m; m &= m - 1) {  // wave-uniform
             const int s = wave - 1 + __builtin_ctzll(m) * (waves - 1);
-            const float z = headz::head_z<HD, FORM>(a.hd, static_cast<int64_t>(b) * K + s, lane, ksl);
+            const int64_t di = static_cast<int64_t>(b) * K + s;
+            const float z = headz::head_z<HD, FORM>(a.hd, di, headz::mapped_row(a.hd, di), lane, ksl);
             if (lane == 0) s_z[s] = z;
         }
     }

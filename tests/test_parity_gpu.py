@@ -1143,3 +1143,16 @@ def test_split_t1_first_phase_outputs(B, K, V):
     first = dict(sb.features, tgt_candidate=sb.candidates)
     _same(whole, first, ["tgt_argmax", "tgt_max", "tgt_lse", "tgt_entropy", "tgt_candidate", "delta", "logp_tgt"])
     assert not first["delta"][0, 0] and torch.isnan(first["logp_tgt"][-1, -1])
+
+
+@pytest.mark.parametrize("B,N,d,h,V,shape", [
+    (3, 20, 512, 65, 4097, "random"),      # 60 nodes, one column past a tile
+    (2, 33, 456, 128, 20001, "star"),      # 66 nodes, a last slice of eight elements, leaves' draft rows unread
+    (9, 64, 1024, 256, 3001, "random"),    # 9 x 4 tiles exactly, 4 groups
+    (40, 30, 512, 512, 40001, "path"),     # 19 x 8 tiles, all of d in one workgroup
+])
+def test_tree_head_tiles(B, N, d, h, V, shape):
+    # trees whose head's first layer runs in tiles over every node, the second on the listed mismatches
+    tr = workloads.make_random_tree(B, N, V, d, h, dtype="bf16", noise=1.3, seed=B + N, bias=True, shape=shape)
+    gpu = _gpu_tree(tr, 0.45, pad=5)
+    parity.check_tree(gpu, _ref_tree(tr, 0.45))
