@@ -175,8 +175,16 @@ def _row_stride(t: torch.Tensor) -> int:
     return int(t.stride(1))
 
 
+# torch's current stream as a raw hipStream_t, without the Stream object that
+# torch.cuda.current_stream() builds on every call (measured: 0.3 against 2.75 us of the 11 us
+# a small call takes).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 class Prepared:
