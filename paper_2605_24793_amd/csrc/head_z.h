@@ -100,14 +100,14 @@ __device__ inline float head_z_cols(const HeadArgs &a, int64_t m, int lane, int 
 }
 
 // z of row m of upart, in every lane of the calling wave, from the first `ksplit` k-slices;
-// NaN when its hidden row id is outside [0, n_rows).  Each column's
+// NaN when the hidden row of its decision slot (or selected row) e is outside [0, n_rows).  Each column's
 // k-slices are summed in slice order (kGroups: in groups of a.zgroup of them, then the
 // groups).  kFew also has the form for at most four slices.  The forms are apart because
 // the chain finish is sensitive to its size: with all of them in one kernel the 8 x K=5
 // step took 15.4 us, with the plain one 14.6.
 enum ZForm { kPlain, kFew, kGroups };
 template <int DT, ZForm FORM>
-__device__ inline float head_z(const HeadArgs &a, int64_t m, int64_t id, int lane, int ksplit) {
+__device__ inline float head_z(const HeadArgs &a, int64_t m, int64_t e, int lane, int ksplit) {
     constexpr bool G = FORM == kGroups;
     float acc;
     if (FORM == kFew && ksplit <= 4)
@@ -116,6 +116,7 @@ __device__ inline float head_z(const HeadArgs &a, int64_t m, int64_t id, int lan
         acc = a.h <= 256 ? head_z_cols<DT, 4, 8, G>(a, m, lane, ksplit) : head_z_cols<DT, 8, 8, G>(a, m, lane, ksplit);
     else
         acc = a.h <= 256 ? head_z_cols<DT, 4, 16, G>(a, m, lane, ksplit) : head_z_cols<DT, 8, 8, G>(a, m, lane, ksplit);
+    const int64_t id = mapped_row(a, e);
     return id >= 0 && id < a.n_rows ? acc + a.b2 : NAN;
 }
 

@@ -256,7 +256,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_chain_finish_head(FinishArgs a) 
         // uses the mismatches' only)
         for (int t = wave - 1; t < K; t += waves - 1) {    // wave-uniform
             const int64_t di = static_cast<int64_t>(b) * K + t;
-            const float z = headz::head_z<HD, FORM>(a.hd, di, headz::mapped_row(a.hd, di), lane, a.hd.ksplit);
+            const float z = headz::head_z<HD, FORM>(a.hd, di, di, lane, a.hd.ksplit);
             if (lane == 0) s_z[t] = z;
         }
     } else {
@@ -279,7 +279,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_chain_finish_head(FinishArgs a) 
         for (uint64_t m = __ballot(need); m; m &= m - 1) {  // wave-uniform
             const int s = wave - 1 + __builtin_ctzll(m) * (waves - 1);
             const int64_t di = static_cast<int64_t>(b) * K + s;
-            const float z = headz::head_z<HD, FORM>(a.hd, di, headz::mapped_row(a.hd, di), lane, ksl);
+            const float z = headz::head_z<HD, FORM>(a.hd, di, di, lane, ksl);
             if (lane == 0) s_z[s] = z;
         }
     }
