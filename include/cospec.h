@@ -161,8 +161,8 @@ typedef struct {
  * GEMM, which derives its list, and the finish), (3) the head on the mismatch
  * rows, (4) finish (draft statistics, log p_D, verdicts, first stop, emission).
  * Chain batches of at most 256 decision slots, and with a bf16 head chain and tree
- * batches whose pre-activations fill at most 256 tiles of 64 slots x 64 columns (those
- * that take no longer than the reduction), run the head's first layer on every slot
+ * batches whose pre-activations fill at most 128 tiles of 64 slots x 64 columns and
+ * whose hidden states are at most 12 MiB, run the head's first layer on every slot
  * inside the reduction's launch instead, and only the mismatches' logits are kept
  * (the reduce events then bracket that launch).
  */

@@ -98,19 +98,20 @@ inline size_t head_bytes(int64_t m_cap, const cospec_head *hd) {
 //  - More while they would outlast the reduction, at about 0.8 us a stage of 32 elements of
 //    d beside it against 6.5 TB/s (16 trees of 38 nodes, 5120 -> 512, 80 tiles, 245 MB: 68.3 with
 //    2 groups, 61.8 with 4, 67.2 after).
-//  - One group, all of d, only when it takes at most half of the reduction (64 trees of 60
-//    nodes, 4096 -> 256, 240 tiles: 294.5 us, 299.1 after; but 256 x K=7, 5120 -> 512, 224 tiles,
-//    195 either way), and up to one workgroup per CU.
+//  - Never one group (all of d), and no more than kMostHidden of hidden states: those tiles
+//    gain little and, on a first pass over new buffers, outlast the reduction (64 trees of 60
+//    nodes, 4096 -> 256, 240 tiles, 31 MB: repeated passes 299.1 -> 294.9 us, a first one 336 ->
+//    360; 32 such trees, 120 tiles, 16 MB: 173.6 -> 165.3, but 186 -> 199; 128 x K=7, 5120 ->
+//    512, 9 MB: 115.8 -> 104.3 and 136 -> 124).
 int32_t head_tile_groups(int64_t m_cap, const cospec_head *hd, int64_t logit_bytes) {
-    constexpr int64_t kCus = 256;
+    constexpr int64_t kCus = 256, kMostHidden = 12 << 20;
     if (hd->dtype != COSPEC_BF16 || m_cap < kTilesMinSlots) return 0;
     const int64_t tiles = (m_cap + kHeadSmallTile - 1) / kHeadSmallTile * ((hd->h + kHeadSmallTile - 1) / kHeadSmallTile);
     // the partials of the eight slices of the form on its own need their place
-    if (tiles > kCus || ksplit_for(m_cap, hd) < kHeadTileSlices) return 0;
+    if (2 * tiles > kCus || m_cap * hd->d * 2 > kMostHidden || ksplit_for(m_cap, hd) < kHeadTileSlices) return 0;
     const double reduce_us = static_cast<double>(logit_bytes) / 6.5e6, tile_us = hd->d / 32 * 0.8;
     int32_t groups = kHeadTileSlices;
     while (tiles * groups > kCus) groups /= 2;
-    if (groups == 1 && tile_us > 0.5 * reduce_us) return 0;
     while (groups < kHeadTileSlices && tile_us > groups * reduce_us) groups *= 2;
     return groups;
 }
@@ -207,8 +208,8 @@ int64_t split_vectors(int64_t nvec, int32_t splits, bool segments) {
 // The partial layout of a step: the caller's split count, or the rule above.  Both
 // phases of a split step derive it from the same arguments.  head_beside: the head's tiles may
 // run beside the reduction; they hold some of the device's places throughout, so that whole
-// rows would end in an uneven last round (256 x K=7, 4096 -> 256: 195.1 us in whole rows, 192
-// in two pieces, 190.6 in four).
+// rows would end in an uneven last round (256 x K=7, 4096 -> 256, with its head in tiles: 195.1 us
+// in whole rows, 192 in two pieces, 190.6 in four).
 PartPlan make_plan(int64_t n_tgt_rows, int64_t n_drf_rows, int64_t nvec, int32_t override_splits, Dtype dt,
                    bool head_beside) {
     PartPlan p{};

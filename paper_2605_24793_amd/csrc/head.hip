@@ -533,7 +533,8 @@ __global__ __launch_bounds__(256) void k_head_epilogue(HeadArgs a, ArbOut o) {
     const int64_t m = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (m >= M) return;
     const int64_t e = a.list ? static_cast<int64_t>(a.list[m]) : m;
-    const float z = headz::head_z<DT, headz::kFew>(a, a.out_by_slot ? e : m, e, threadIdx.x & 63, a.ksplit);
+    // (cospec_arbitrate's rows are list positions: their loads need not wait for the list's)
+    const float z = headz::head_z<DT, headz::kFew>(a, !ARB && a.out_by_slot ? e : m, e, threadIdx.x & 63, a.ksplit);
     if ((threadIdx.x & 63) != 0) return;
     if constexpr (ARB) {
         if (o.z) o.z[m] = z;

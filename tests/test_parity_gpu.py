@@ -1149,7 +1149,8 @@ def test_split_t1_first_phase_outputs(B, K, V):
     (3, 20, 512, 65, 4097, "random"),      # 60 nodes, one column past a tile
     (2, 33, 456, 128, 20001, "star"),      # 66 nodes, a last slice of eight elements, leaves' draft rows unread
     (9, 64, 1024, 256, 3001, "random"),    # 9 x 4 tiles exactly, 4 groups
-    (40, 30, 512, 512, 40001, "path"),     # 19 x 8 tiles, all of d in one workgroup
+    (40, 30, 512, 512, 40001, "path"),     # 19 x 8 tiles: past them, on the mismatch nodes
+    (33, 30, 512, 512, 40001, "path"),     # 16 x 8 tiles, the most, 2 groups
 ])
 def test_tree_head_tiles(B, N, d, h, V, shape):
     # trees whose head's first layer runs in tiles over every node, the second on the listed mismatches
