@@ -728,7 +728,9 @@ constexpr int64_t kMinChunk = 128;    // keys of a piece, at least
 // about 3 TB/s.  The cost agrees with the measured times of 16 to 256 groups, cut 1 to 32
 // times, within 3 us: 16 groups x 16401 keys 330 us uncut, 32.0 in 256 workgroups, 34.0 in
 // 512; 64 x 4017 31.5 in 256, 36.1 in 512; 96 x 2517 36.9 in 192, 32.5 in 480; 160 x 4113
-// 87 uncut, 79 in 320, 65 in 480; 224 x 2017 46 uncut, 53 in 448.  More groups than CUs are
+// 87 uncut, 79 in 320, 65 in 480; 224 x 2017 46 uncut, 53 in 448.  Short contexts are not cut:
+// a call of two launches takes 13.5 us at the least (8 groups, D = 128: 417 keys 13.0 uncut, 537
+// keys 15.1 uncut and 13.5 cut; D = 64: 537 keys 11.9 uncut, 717 15.1).  More groups than CUs are
 // not cut: two of them already share a CU.
 AttnPlan attn_plan(int32_t B, int32_t n_q, int32_t L, int32_t Hq, int32_t Hkv, int32_t D) {
     AttnPlan p{1, 0, 0};
@@ -740,6 +742,7 @@ AttnPlan attn_plan(int32_t B, int32_t n_q, int32_t L, int32_t Hq, int32_t Hkv, i
     const double t1 = D == 128 ? 0.023 : 0.0185, t2 = D == 128 ? 0.037 : 0.022;
     const double piece_us = static_cast<double>(std::min<int64_t>(rows, 16 * waves)) * D * 8 / 3e6;
     double best = L * t1;
+    if (best < 10.5) return p;
     for (int64_t s = 2; s <= 64 && wgs * s <= 2 * kCus; ++s) {
         const int64_t chunk = ((L + s - 1) / s + kKeyBlock - 1) / kKeyBlock * kKeyBlock;
         if (chunk < kMinChunk) break;

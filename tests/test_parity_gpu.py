@@ -995,7 +995,7 @@ def test_hybrid_attention_long_prefill_several_workgroups():
 
 
 @pytest.mark.parametrize("B,nq,Hq,Hkv,D,ctx,L,K", [
-    (1, 17, 8, 2, 128, [128 * 3 - 17], 384, 7),        # whole pieces exactly
+    (1, 17, 8, 2, 128, [128 * 5 - 17], 640, 7),        # whole pieces exactly
     (2, 11, 7, 1, 64, [1500, 130], 1530, 4),           # a sequence that ends inside the second piece
     (2, 17, 4, 4, 128, [2047, 0], 2064, 7),            # no context at all beside a long one
     (1, 40, 8, 2, 128, [600], 700, 20),                # queries past the input, two workgroups per group
