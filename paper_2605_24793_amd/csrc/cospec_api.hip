@@ -84,8 +84,8 @@ inline int32_t ksplit_for(int64_t m_cap, const cospec_head *hd) {
 
 // cospec_arbitrate's scratch: k-slice partial pre-activations.
 inline size_t head_bytes(int64_t m_cap, const cospec_head *hd) {
-    return round_up(static_cast<size_t>(ksplit_for(m_cap, hd)) * static_cast<size_t>(m_cap) *
-                    static_cast<size_t>(hd->h) * 4);
+    return round_up(static_cast<size_t>(head_alone_ksplit(m_cap, hd->d, hd->h, elem_bytes(hd->dtype))) *
+                    static_cast<size_t>(m_cap) * static_cast<size_t>(hd->h) * 4);
 }
 
 // Steps whose head's first layer runs in tiles over every decision slot, beside the reduction
@@ -898,7 +898,7 @@ cospec_status cospec_arbitrate(const void *hidden, int64_t n_rows, const int32_t
     const size_t need = cospec_arbitrate_workspace_size(n_sel, head);
     if (!workspace || !aligned(workspace, kAlign) || workspace_bytes < need) return COSPEC_ERR_WORKSPACE;
 
-    const int32_t ks = ksplit_for(n_sel, head);
+    const int32_t ks = head_alone_ksplit(n_sel, head->d, head->h, elem_bytes(head->dtype));
     float *upart = static_cast<float *>(workspace);
     HeadArgs ha{};
     ha.hidden = hidden; ha.n_rows = n_rows; ha.list = row_index;

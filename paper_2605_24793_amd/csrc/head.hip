@@ -26,6 +26,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "head_z.h"
@@ -548,10 +549,11 @@ __global__ __launch_bounds__(256) void k_head_epilogue(HeadArgs a, ArbOut o) {
 
 // k-slices of d: one per XCD (each XCD's L2 then holds one slice of the hidden rows
 // and of W1), more, in multiples of the XCD count, while the tiles times slices stay
-// below one workgroup per CU; fewer when the tiles alone give every CU two workgroups of
-// the shallow ring, so that no more partials are written and read back than that takes
-// (4096 rows, 5120 -> 512, 128 tiles: GEMM + second layer 36.4 + 13.4 us in 8 slices, 26.5 +
-// 8.9 in 4, 29.1 + 7.7 in 2, 45.2 + 7.2 in 1); never more than there are stages of d.
+// below one workgroup per CU; never more than there are stages of d.  A step's count rests
+// on its decision slots alone: how few of them are mismatches only the device knows, and
+// the persistent GEMM cuts the slices further when its rows need it (headz::live_ksplit).
+// Taking slices off here while all slots' tiles exceeded two workgroups per CU left CUs idle
+// when few slots mismatched: 256 x K=40, 5120 -> 512, 3% mismatches 159 us against 135.
 int32_t head_ksplit(int64_t m_cap, int32_t d, int32_t h, int32_t elem_bytes) {
     const int64_t mt = (m_cap + kHeadTileM - 1) / kHeadTileM;
     const int64_t nt = (h + kHeadTileN - 1) / kHeadTileN;
@@ -559,10 +561,19 @@ int32_t head_ksplit(int64_t m_cap, int32_t d, int32_t h, int32_t elem_bytes) {
     const int64_t stages = (static_cast<int64_t>(d) * elem_bytes + kStageBytes - 1) / kStageBytes;
     int64_t ks = kXcds;
     while (ks + kXcds <= kHeadMaxSplit && mt * nt * (ks + kXcds) <= kHeadTargetBlocks) ks += kXcds;
-    if (mt * nt * ks > kHeadMostBlocks) ks = kHeadMostBlocks / (mt * nt);
     if (ks > stages) ks = stages;
     if (ks < 1) ks = 1;
     return static_cast<int32_t>(ks);
+}
+
+// The slices of cospec_arbitrate, where every row is live: fewer when the tiles alone give
+// every CU two workgroups of the shallow ring, so that no more partials are written and read
+// back than that takes (4096 rows, 5120 -> 512, 128 tiles: GEMM + second layer 36.4 + 13.4 us
+// in 8 slices, 26.5 + 8.9 in 4, 29.1 + 7.7 in 2, 45.2 + 7.2 in 1).
+int32_t head_alone_ksplit(int64_t n_sel, int32_t d, int32_t h, int32_t elem_bytes) {
+    const int64_t tiles = (n_sel + kHeadTileM - 1) / kHeadTileM * ((h + kHeadTileN - 1) / kHeadTileN);
+    const int32_t ks = head_ksplit(n_sel, d, h, elem_bytes);
+    return tiles * ks <= kHeadMostBlocks ? ks : std::max<int32_t>(1, std::min<int32_t>(ks, kHeadMostBlocks / tiles));
 }
 
 int32_t head_gemm_slots(Dtype dt, bool build) {

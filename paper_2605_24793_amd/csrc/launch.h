@@ -16,7 +16,7 @@ constexpr int kHeadTileN = 128;       //                            columns of W
 // per step; 256 gained less and cost the large chain batch 0.5 us)
 constexpr int kHeadTargetBlocks = 128;
 constexpr int kHeadMaxSplit = 32;
-constexpr int kHeadMostBlocks = 512;  // slices are taken off while the grid exceeds two workgroups per CU
+constexpr int kHeadMostBlocks = 512;  // cospec_arbitrate: no more workgroups than two per CU
 constexpr int kHeadSmallTile = 64;    // the tiles of the first layer beside the reduction
 constexpr int kHeadTileSlices = 8;    // ... and the slices of d they sum by themselves
 constexpr int kXcds = 8;             // MI355X: 8 XCDs, each with its own L2
@@ -295,6 +295,7 @@ int32_t reduce_slots(Dtype dt);   // reduction workgroups resident at once on th
 hipError_t launch_sample(Dtype dt, const SampleArgs &a, hipStream_t s);
 hipError_t launch_decide(Dtype dt, const DecideArgs &a, hipStream_t s);
 int32_t head_ksplit(int64_t m_cap, int32_t d, int32_t h, int32_t elem_bytes);
+int32_t head_alone_ksplit(int64_t n_sel, int32_t d, int32_t h, int32_t elem_bytes);   // cospec_arbitrate
 // GEMM + epilogue: z of the listed rows, or cospec_arbitrate's outputs when out is given.
 hipError_t launch_head(Dtype dt, const HeadArgs &a, const ArbOut *out, hipStream_t s);
 hipError_t launch_head_epilogue(Dtype dt, const HeadArgs &a, const ArbOut *out, hipStream_t s);

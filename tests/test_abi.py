@@ -67,6 +67,20 @@ def test_workspace_sizes():
     assert L.cospec_verify_block_workspace_size(1, 4, 100, ctypes.byref(bad)) == 0
 
 
+@pytest.mark.parametrize("K", [10, 15, 20])
+def test_a_large_batchs_workspace_serves_smaller_ones(K):
+    # the head's k-slices of a step must not fall with its decision slots: a program that sizes
+    # one workspace for its largest batch runs every smaller one in it, and what the static
+    # scratch buffer does not hold stays refused
+    L = cs.lib()
+    hd = _head(d=5120, h=512)
+    size = lambda B: L.cospec_verify_block_workspace_size(B, K, 32000, ctypes.byref(hd))  # noqa: E731
+    assert max(size(B) for B in range(1, 257)) == size(256) >= 8 * 256 * K * 512 * 4
+    args = [FAKE, FAKE, 1, 32000, FAKE, FAKE, ctypes.byref(hd), 0.5]
+    if K == 20:
+        assert L.cospec_verify_block_static(*args, 256, K, 32000, FAKE, FAKE, None, None, None) == -5
+
+
 @pytest.mark.parametrize("B,K,V", [(64, 7, 151936), (256, 7, 151936), (1, 4, 32000), (8, 5, 128256),
                                    (0, 7, 100), (5, 0, 1000), (300, 64, 9)])
 def test_generic_workspace_query_matches_the_per_entry_queries(B, K, V):
