@@ -82,10 +82,11 @@ inline int32_t ksplit_for(int64_t m_cap, const cospec_head *hd) {
     return hd ? head_ksplit(m_cap, hd->d, hd->h, elem_bytes(hd->dtype)) : 0;   // no head: no scratch
 }
 
-// cospec_arbitrate's scratch: k-slice partial pre-activations.
+// cospec_arbitrate's scratch: k-slice partial pre-activations, room for every slice also where
+// a workgroup sums several, so that the size grows with the rows.
 inline size_t head_bytes(int64_t m_cap, const cospec_head *hd) {
-    return round_up(static_cast<size_t>(head_alone_ksplit(m_cap, hd->d, hd->h, elem_bytes(hd->dtype))) *
-                    static_cast<size_t>(m_cap) * static_cast<size_t>(hd->h) * 4);
+    return round_up(static_cast<size_t>(ksplit_for(m_cap, hd)) * static_cast<size_t>(m_cap) *
+                    static_cast<size_t>(hd->h) * 4);
 }
 
 // Steps whose head's first layer runs in tiles over every decision slot, beside the reduction
@@ -898,13 +899,16 @@ cospec_status cospec_arbitrate(const void *hidden, int64_t n_rows, const int32_t
     const size_t need = cospec_arbitrate_workspace_size(n_sel, head);
     if (!workspace || !aligned(workspace, kAlign) || workspace_bytes < need) return COSPEC_ERR_WORKSPACE;
 
-    const int32_t ks = head_alone_ksplit(n_sel, head->d, head->h, elem_bytes(head->dtype));
+    const int32_t slices = ksplit_for(n_sel, head);
+    const int32_t per = head_alone_group(n_sel, n_rows, head->d, head->h, elem_bytes(head->dtype));
+    const int32_t ks = (slices + per - 1) / per;
     float *upart = static_cast<float *>(workspace);
     HeadArgs ha{};
     ha.hidden = hidden; ha.n_rows = n_rows; ha.list = row_index;
     ha.count_dev = nullptr; ha.count_host = n_sel; ha.m_cap = n_sel;
     ha.w1 = head->w1; ha.b1 = head->b1; ha.w2 = head->w2; ha.b2 = head->b2; ha.d = head->d; ha.h = head->h;
     ha.ksplit = ks;
+    if (per > 1) { ha.kslices = slices; ha.kgroup = per; }
     // the row count is known here: the shallow ring when the grid has more workgroups
     // than there are CUs
     ha.two_per_cu = ((n_sel + kHeadTileM - 1) / kHeadTileM) * ((head->h + kHeadTileN - 1) / kHeadTileN) * ks >

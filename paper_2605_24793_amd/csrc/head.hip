@@ -61,8 +61,26 @@ __device__ inline void load_lds16(const void *g, const char *lds) {
                  : "s"(base), "v"(g)
                  : "memory", "m0");
 }
+// The same from a raw buffer at byte offset `off`: zeros past the buffer's end.
+__device__ inline void load_lds16(u32x4 rsrc, uint32_t off, const char *lds) {
+    const uint32_t base =
+        __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_char *)lds)));
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 :
+                 : "s"(base), "v"(off), "s"(rsrc)
+                 : "memory", "m0");
+}
 #pragma clang diagnostic pop
 
+// A raw buffer (stride 0, 32-bit data format) of `bytes` bytes, the same in every lane.
+__device__ inline u32x4 raw_rsrc(const void *p, uint32_t bytes) {
+    const uint64_t addr = reinterpret_cast<uint64_t>(p);
+    auto uniform = [](uint64_t x) { return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(x))); };
+    return u32x4{uniform(addr), uniform(addr >> 32) & 0xffffu, uniform(bytes), 0x00020000u};
+}
+
+constexpr uint32_t kRawPast = 0xfffffff0u;        // an offset past the end of every raw buffer here
+constexpr int64_t kRawMax = kRawPast;
 constexpr int kStageBytes = 128;                  // bytes of k per row per stage
 // LDS ring depth: four stages (three in flight while one is used, 128 KiB: one
 // workgroup per CU), or two (64 KiB: two workgroups per CU) when the grid has more
@@ -264,9 +282,11 @@ __device__ inline int64_t build_list(const HeadArgs &a, int32_t *list) {
 // lid: the list entries of this lane's two loader rows (m past M: anything).  With
 // out_by_slot the stores go by list entry (the decision slot), read from s_list (the
 // whole list in LDS) or else from s_rows, where this function puts the tile's entries.
-template <int DT, int kRing>
+// SUMS: the k-range is several slices of `slice_st` stages each; every slice is summed by itself
+// and the sums are added in order, so that no sum runs over more than a slice of d.
+template <int DT, int kRing, bool SUMS>
 __device__ inline void gemm_tile(const HeadArgs &a, int64_t M, int64_t m_base, int n_base, int ks, int k0, int k1,
-                                 const int32_t lid[2], const int32_t *s_list, int32_t *s_rows,
+                                 int slice_st, const int32_t lid[2], const int32_t *s_list, int32_t *s_rows,
                                  char (*ring)[2 * kHeadTileM * kStageBytes]) {
     constexpr int EB = DT == kBF16 ? 2 : 4;
     constexpr int BK = kStageBytes / EB;          // elements of k per stage
@@ -289,6 +309,7 @@ __device__ inline void gemm_tile(const HeadArgs &a, int64_t M, int64_t m_base, i
     // each); lane l brings row 8*(w*2+i) + l/8, k-vector (l%8) ^ (row%8)
     const char *ga[2];
     const char *gb[2];
+    uint32_t oa[2], ob[2];                        // SUMS: byte offsets in raw buffers
     int lvec[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -302,7 +323,11 @@ __device__ inline void gemm_tile(const HeadArgs &a, int64_t M, int64_t m_base, i
         int n = n_base + row;
         if (n >= a.h) n = a.h - 1;
         gb[i] = static_cast<const char *>(a.w1) + static_cast<int64_t>(n) * a.d * EB;
+        oa[i] = static_cast<uint32_t>(id) * a.d * EB;
+        ob[i] = static_cast<uint32_t>(n) * a.d * EB;
     }
+    const u32x4 ra = raw_rsrc(a.hidden, static_cast<uint32_t>(a.n_rows) * a.d * EB);
+    const u32x4 rb = raw_rsrc(a.w1, static_cast<uint32_t>(a.h) * a.d * EB);
     // Branch-free: a lane past the ragged end of d (d is a multiple of VE) loads the zero
     // vector instead, so a stage's loads are one straight run of instructions.
     auto issue = [&](int st) {
@@ -313,6 +338,11 @@ __device__ inline void gemm_tile(const HeadArgs &a, int64_t M, int64_t m_base, i
             char *la = slot + (wave * 2 + i) * 1024;
             char *lb = slot + kHeadTileM * kStageBytes + (wave * 2 + i) * 1024;
             const bool in = e < k1;
+            if constexpr (SUMS) {                               // past the end of d: past the buffers' too
+                load_lds16(ra, in ? oa[i] + e * EB : kRawPast, la);
+                load_lds16(rb, in ? ob[i] + e * EB : kRawPast, lb);
+                continue;
+            }
             const char *pa = in ? ga[i] + static_cast<int64_t>(e) * EB : reinterpret_cast<const char *>(kZeroVec);
             const char *pb = in ? gb[i] + static_cast<int64_t>(e) * EB : reinterpret_cast<const char *>(kZeroVec);
             load_lds16(pa, la);
@@ -320,11 +350,26 @@ __device__ inline void gemm_tile(const HeadArgs &a, int64_t M, int64_t m_base, i
         }
     };
 
-    floatx4 acc[4][2];
+    floatx4 acc[4][2], sum[4][2];
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int c = 0; c < 2; ++c) acc[r][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int c = 0; c < 2; ++c) acc[r][c] = sum[r][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+    int left = slice_st;                          // stages of the slice still to come
+    auto end_stage = [&]() {
+        if constexpr (SUMS) {
+            if (--left == 0) {                    // wave-uniform
+                left = slice_st;
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+                        sum[r][c] += acc[r][c];
+                        acc[r][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+                    }
+            }
+        }
+    };
 
     // Fragments of one 64-byte k-step q of stage st: this wave's 4 row tiles of A and 2
     // column tiles of B.
@@ -395,6 +440,7 @@ __device__ inline void gemm_tile(const HeadArgs &a, int64_t M, int64_t m_base, i
         __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+        end_stage();
     }
     for (; st < nst; ++st) {                                    // the last kRing stages
         read_frags(st, 1, a1, b1);
@@ -409,6 +455,13 @@ __device__ inline void gemm_tile(const HeadArgs &a, int64_t M, int64_t m_base, i
         }
         __builtin_amdgcn_sched_barrier(0);
         products(a1, b1);
+        end_stage();
+    }
+    if constexpr (SUMS) {                         // a last slice of fewer stages
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) acc[r][c] += sum[r][c];
     }
 
     // partial U of this k-slice: upart[ks][row][n], row the list position m, or with
@@ -437,8 +490,11 @@ __device__ inline void gemm_tile(const HeadArgs &a, int64_t M, int64_t m_base, i
 // workgroups past M leave.  1-D grid, k-slice fastest: workgroups are dealt to the 8
 // XCDs round-robin, so with 8 slices each XCD owns one slice of the hidden rows and of
 // W1, which fits its L2.
-template <int DT, int kRing>
-__global__ __launch_bounds__(64 * kGemmWaves) void k_head_gemm(HeadArgs a) {
+// SUMS (cospec_arbitrate): a workgroup takes a.kgroup consecutive slices.  Its second set of sums
+// costs 32 registers; raw buffers in place of pointers leave it two workgroups per CU.
+template <int DT, int kRing, bool SUMS>
+__global__ __launch_bounds__(64 * kGemmWaves) __attribute__((amdgpu_waves_per_eu(kRing == kRingShallow ? 4 : 2)))
+void k_head_gemm(HeadArgs a) {
     constexpr int BK = kStageBytes / (DT == kBF16 ? 2 : 4);
     __shared__ __attribute__((aligned(16))) char ring[kRing][2 * kHeadTileM * kStageBytes];
     __shared__ int32_t s_rows[kHeadTileM];
@@ -458,10 +514,11 @@ __global__ __launch_bounds__(64 * kGemmWaves) void k_head_gemm(HeadArgs a) {
     }
     const int64_t M = a.count_dev ? static_cast<int64_t>(*a.count_dev) : a.count_host;
     if (m_base >= M) return;
-    const int kchunk = ((a.d + a.ksplit - 1) / a.ksplit + BK - 1) / BK * BK;
+    const int slices = SUMS ? a.kslices : a.ksplit;
+    const int kslice = ((a.d + slices - 1) / slices + BK - 1) / BK * BK, kchunk = SUMS ? a.kgroup * kslice : kslice;
     const int k0 = ks * kchunk;
-    gemm_tile<DT, kRing>(a, M, m_base, (tile / mtiles) * kHeadTileN, ks, k0, min(a.d, k0 + kchunk), lid, nullptr,
-                         s_rows, ring);
+    gemm_tile<DT, kRing, SUMS>(a, M, m_base, (tile / mtiles) * kHeadTileN, ks, k0, min(a.d, k0 + kchunk),
+                               kslice / BK, lid, nullptr, s_rows, ring);
 }
 
 // Persistent GEMM (chains): a.grid workgroups loop over the (tile, k-slice) items of
@@ -503,8 +560,8 @@ __global__ __launch_bounds__(64 * kGemmWaves) void k_head_gemm_loop(HeadArgs a) 
             lid[i] = BUILD ? s_list[m] : a.list[m];
         }
         const int k0 = ks * kchunk;
-        gemm_tile<DT, kRing>(a, M, m_base, (tile / mt) * kHeadTileN, ks, k0, min(a.d, k0 + kchunk), lid,
-                             BUILD ? s_list : nullptr, s_rows, ring);
+        gemm_tile<DT, kRing, false>(a, M, m_base, (tile / mt) * kHeadTileN, ks, k0, min(a.d, k0 + kchunk),
+                                    kchunk / BK, lid, BUILD ? s_list : nullptr, s_rows, ring);
         __syncthreads();          // the ring and s_rows are the next item's
     }
 }
@@ -566,14 +623,21 @@ int32_t head_ksplit(int64_t m_cap, int32_t d, int32_t h, int32_t elem_bytes) {
     return static_cast<int32_t>(ks);
 }
 
-// The slices of cospec_arbitrate, where every row is live: fewer when the tiles alone give
-// every CU two workgroups of the shallow ring, so that no more partials are written and read
-// back than that takes (4096 rows, 5120 -> 512, 128 tiles: GEMM + second layer 36.4 + 13.4 us
-// in 8 slices, 26.5 + 8.9 in 4, 29.1 + 7.7 in 2, 45.2 + 7.2 in 1).
-int32_t head_alone_ksplit(int64_t n_sel, int32_t d, int32_t h, int32_t elem_bytes) {
+// How many consecutive slices one workgroup of cospec_arbitrate sums, where every row is live:
+// as few (a power of two) as leave no more workgroups than two per CU, so that no more partials
+// are written and read back than the grid needs.  A workgroup sums every slice by itself
+// (gemm_tile's SUMS), so the sums run no longer than a step's; without that the relative error
+// of z grew from 1.6e-7 to 2.1e-7 at 4096 rows.  Whole calls, 5120 -> 512: 2300 rows 28.2 us with
+// two slices a workgroup, 32.8 with one; 4096 rows 33.9 and 48.2; 8192 rows 60.1 with four, 71.7
+// with one.  fp32 heads, whose products are sixteen times as slow, are bound by them and lose
+// with fewer workgroups (3000 rows 168.7 us against 140.5): one slice each.
+int32_t head_alone_group(int64_t n_sel, int64_t n_rows, int32_t d, int32_t h, int32_t elem_bytes) {
     const int64_t tiles = (n_sel + kHeadTileM - 1) / kHeadTileM * ((h + kHeadTileN - 1) / kHeadTileN);
-    const int32_t ks = head_ksplit(n_sel, d, h, elem_bytes);
-    return tiles * ks <= kHeadMostBlocks ? ks : std::max<int32_t>(1, std::min<int32_t>(ks, kHeadMostBlocks / tiles));
+    const int64_t ks = head_ksplit(n_sel, d, h, elem_bytes), row = static_cast<int64_t>(d) * elem_bytes;
+    if (elem_bytes != 2 || n_rows * row > kRawMax || h * row > kRawMax) return 1;   // raw buffers: 32-bit offsets
+    int64_t per = 1;
+    while (per < ks && tiles * ((ks + per - 1) / per) > kHeadMostBlocks) per *= 2;
+    return static_cast<int32_t>(std::min(per, ks));
 }
 
 int32_t head_gemm_slots(Dtype dt, bool build) {
@@ -644,12 +708,15 @@ hipError_t launch_head_gemm(Dtype dt, const HeadArgs &a, hipStream_t s) {
     const int64_t tiles = ((a.m_cap + kHeadTileM - 1) / kHeadTileM) * ((a.h + kHeadTileN - 1) / kHeadTileN);
     const dim3 grid(static_cast<unsigned>(tiles * a.ksplit));
     if (grid.x == 0) return hipSuccess;
-    if (a.two_per_cu) {
-        if (dt == kBF16) hipLaunchKernelGGL((k_head_gemm<kBF16, kRingShallow>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k_head_gemm<kF32, kRingShallow>), grid, block, 0, s, a);
+    if (a.kslices > 0) {                                // several slices each (more than two workgroups per CU)
+        if (dt != kBF16) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((k_head_gemm<kBF16, kRingShallow, true>), grid, block, 0, s, a);
+    } else if (a.two_per_cu) {
+        if (dt == kBF16) hipLaunchKernelGGL((k_head_gemm<kBF16, kRingShallow, false>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((k_head_gemm<kF32, kRingShallow, false>), grid, block, 0, s, a);
     } else {
-        if (dt == kBF16) hipLaunchKernelGGL((k_head_gemm<kBF16, kRingDeep>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k_head_gemm<kF32, kRingDeep>), grid, block, 0, s, a);
+        if (dt == kBF16) hipLaunchKernelGGL((k_head_gemm<kBF16, kRingDeep, false>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((k_head_gemm<kF32, kRingDeep, false>), grid, block, 0, s, a);
     }
     return hipGetLastError();
 }

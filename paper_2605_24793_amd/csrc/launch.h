@@ -144,6 +144,7 @@ struct HeadArgs {
     // kHeadTileSlices slices of d that one workgroup sums, and how many consecutive stored
     // slices the second layer sums before it adds them up (powers of two).
     int32_t kgroup, zgroup;
+    int32_t kslices;           // cospec_arbitrate: slices of d when a workgroup sums kgroup of them; else 0
     int32_t grid;              // chains: workgroups of the persistent GEMM (at most one per
                                // resident slot); 0: one workgroup per (tile, k-slice)
     int32_t two_per_cu;        // use the shallow LDS ring: two workgroups fit on a CU
@@ -295,7 +296,7 @@ int32_t reduce_slots(Dtype dt);   // reduction workgroups resident at once on th
 hipError_t launch_sample(Dtype dt, const SampleArgs &a, hipStream_t s);
 hipError_t launch_decide(Dtype dt, const DecideArgs &a, hipStream_t s);
 int32_t head_ksplit(int64_t m_cap, int32_t d, int32_t h, int32_t elem_bytes);
-int32_t head_alone_ksplit(int64_t n_sel, int32_t d, int32_t h, int32_t elem_bytes);   // cospec_arbitrate
+int32_t head_alone_group(int64_t n_sel, int64_t n_rows, int32_t d, int32_t h, int32_t elem_bytes);   // cospec_arbitrate
 // GEMM + epilogue: z of the listed rows, or cospec_arbitrate's outputs when out is given.
 hipError_t launch_head(Dtype dt, const HeadArgs &a, const ArbOut *out, hipStream_t s);
 hipError_t launch_head_epilogue(Dtype dt, const HeadArgs &a, const ArbOut *out, hipStream_t s);

@@ -81,6 +81,13 @@ def test_a_large_batchs_workspace_serves_smaller_ones(K):
         assert L.cospec_verify_block_static(*args, 256, K, 32000, FAKE, FAKE, None, None, None) == -5
 
 
+def test_arbitrates_workspace_grows_with_its_rows():
+    L = cs.lib()
+    hd = _head(d=5120, h=512)
+    size = [L.cospec_arbitrate_workspace_size(n, ctypes.byref(hd)) for n in range(1, 8300)]
+    assert max(size[:4096]) <= size[4096] and max(size) == size[-1]
+
+
 @pytest.mark.parametrize("B,K,V", [(64, 7, 151936), (256, 7, 151936), (1, 4, 32000), (8, 5, 128256),
                                    (0, 7, 100), (5, 0, 1000), (300, 64, 9)])
 def test_generic_workspace_query_matches_the_per_entry_queries(B, K, V):

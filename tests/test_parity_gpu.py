@@ -1049,14 +1049,14 @@ def test_hybrid_attention_many_rows_scale(scale):
 
 
 @pytest.mark.parametrize("n,d,h,dtype", [
-    (16384 + 5, 64, 128, "bf16"),      # 129 row tiles: 3 k-slices, but only one stage of d
-    (8193, 512, 130, "bf16"),          # 65 x 2 tiles: 3 slices
-    (4097, 264, 300, "f32"),           # 33 x 3 tiles of a wide fp32 head: 5 slices, a ragged last one
+    (16384 + 5, 64, 128, "bf16"),      # 129 row tiles, one stage of d: one slice
+    (8193, 512, 130, "bf16"),          # 65 x 2 tiles: eight slices, four a workgroup
+    (4097, 264, 300, "f32"),           # 33 x 3 tiles of a wide fp32 head: eight slices, a ragged last one
     (1, 64, 1, "bf16"),                # one row, one column
     (129, 4096, 512, "bf16"),          # few tiles: 16 slices
 ])
 def test_arbitrate_slices(n, d, h, dtype):
-    # how many k-slices a call takes depends on its row count; z against float64, NaN and a
+    # how many k-slices a call takes, and a workgroup of them, depends on its row count; z against float64, NaN and a
     # rejection at indices off either end
     g = torch.Generator().manual_seed(n)
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
@@ -1076,6 +1076,23 @@ def test_arbitrate_slices(n, d, h, dtype):
     assert (z[ok] - ref[ok]).abs().max() <= 2.0 ** -24 * (d + h) * max(1.0, float(ref.abs().max()))
     clear = ok & ((torch.sigmoid(ref) - 0.5).abs() > 1e-3)
     assert torch.equal(acc[clear].bool(), torch.sigmoid(ref[clear]) > 0.5)
+
+
+@pytest.mark.parametrize("n,d,h", [(4096, 5120, 512), (9000, 392, 130)])
+def test_arbitrate_error_does_not_grow_with_rows(n, d, h):
+    # many rows: a workgroup takes several k-slices (a ragged last one of eight elements in the
+    # second case).  Each is summed by itself, so that z is as exact as in calls of few rows,
+    # which take one slice per workgroup; with sums over the whole range the first case's error
+    # was 1.2 times as large, now 0.97 to 1.0.
+    g = torch.Generator(device=DEV).manual_seed(n)
+    rnd = lambda *s: torch.randn(*s, generator=g, device=DEV)  # noqa: E731
+    hid = rnd(n, d).bfloat16()
+    head = workloads.Head((rnd(h, d) / d ** 0.5).bfloat16(), rnd(h).bfloat16(), (rnd(h) / h ** 0.5).bfloat16(), 0.25)
+    many = cs.arbitrate(hid, head, 0.5)["z"].double()
+    few = torch.cat([cs.arbitrate(hid[r:r + 512], head, 0.5)["z"] for r in range(0, n, 512)]).double()
+    ref = (hid.double() @ head.w1.double().t().contiguous() + head.b1.double()).clamp(min=0) @ head.w2.double() + 0.25
+    err = lambda z: (z - ref).norm().item() / ref.norm().item()  # noqa: E731
+    assert err(few) < 1e-6 and err(many) <= 1.1 * err(few)
 
 
 @pytest.mark.parametrize("B,K,noise", [(40, 11, 0.9), (24, 12, 0.9), (12, 22, 3.0), (12, 23, 0.2), (5, 64, 1.5)])
