@@ -108,12 +108,12 @@ int32_t head_tile_groups(int64_t m_cap, const cospec_head *hd, int64_t logit_byt
     constexpr int64_t kCus = 256, kMostHidden = 12 << 20;
     if (hd->dtype != COSPEC_BF16 || m_cap < kTilesMinSlots) return 0;
     const int64_t tiles = (m_cap + kHeadSmallTile - 1) / kHeadSmallTile * ((hd->h + kHeadSmallTile - 1) / kHeadSmallTile);
-    // the partials of the eight slices of the form on its own need their place
-    if (2 * tiles > kCus || m_cap * hd->d * 2 > kMostHidden || ksplit_for(m_cap, hd) < kHeadTileSlices) return 0;
+    // at least eight slices, and a place for their partials in the form on its own
+    if (2 * tiles > kCus || m_cap * hd->d * 2 > kMostHidden || ksplit_for(m_cap, hd) < kHeadTileGroups) return 0;
     const double reduce_us = static_cast<double>(logit_bytes) / 6.5e6, tile_us = hd->d / 32 * 0.8;
-    int32_t groups = kHeadTileSlices;
+    int32_t groups = kHeadTileGroups;
     while (tiles * groups > kCus) groups /= 2;
-    while (groups < kHeadTileSlices && tile_us > groups * reduce_us) groups *= 2;
+    while (groups < kHeadTileGroups && tile_us > groups * reduce_us) groups *= 2;
     return groups;
 }
 
@@ -350,9 +350,13 @@ cospec_status run(const Common &c, Phase phase, int32_t *accept_len, int32_t *ou
         if (every_slot && ha.ksplit > kEverySlotSplits) ha.ksplit = kEverySlotSplits;
         if (tiles) {
             // beside the reduction a workgroup sums a whole group of slices; on its own, one
-            // slice, and the second layer sums the groups
-            const int32_t per = kHeadTileSlices / tile_groups;
-            ha.ksplit = phase == kWhole ? tile_groups : kHeadTileSlices;
+            // slice, and the second layer sums the groups.  Slices: a power of two no larger than
+            // the other forms' count (whose partials fit the workspace)
+            const int32_t most = c.is_tree ? 32 : kEverySlotSplits;
+            ha.kslices = kHeadTileGroups;
+            while (2 * ha.kslices <= ha.ksplit && ha.kslices < most) ha.kslices *= 2;
+            const int32_t per = ha.kslices / tile_groups;
+            ha.ksplit = phase == kWhole ? tile_groups : ha.kslices;
             ha.kgroup = phase == kWhole ? per : 1;
             ha.zgroup = phase == kWhole ? 1 : per;
         }

@@ -680,7 +680,7 @@ hipError_t launch_slot_gemm(Dtype dt, const HeadArgs &a, hipStream_t s) {
 }
 
 hipError_t launch_tile_gemm(const HeadArgs &a, hipStream_t s) {
-    if (a.m_cap <= 0 || a.m_cap > slotgemm::kMaxSlots || a.ksplit * a.kgroup != kHeadTileSlices) return hipErrorInvalidValue;
+    if (a.m_cap <= 0 || a.m_cap > slotgemm::kMaxSlots || a.kslices < 1 || a.ksplit * a.kgroup != a.kslices) return hipErrorInvalidValue;
     const int64_t blocks = tilegemm::blocks(a);
     if (blocks > INT32_MAX) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_tile_gemm, dim3(static_cast<unsigned>(blocks)), dim3(kReduceThreads), 0, s, a);
@@ -708,7 +708,7 @@ hipError_t launch_head_gemm(Dtype dt, const HeadArgs &a, hipStream_t s) {
     const int64_t tiles = ((a.m_cap + kHeadTileM - 1) / kHeadTileM) * ((a.h + kHeadTileN - 1) / kHeadTileN);
     const dim3 grid(static_cast<unsigned>(tiles * a.ksplit));
     if (grid.x == 0) return hipSuccess;
-    if (a.kslices > 0) {                                // several slices each (more than two workgroups per CU)
+    if (a.kgroup > 1) {                                 // several slices each (more than two workgroups per CU)
         if (dt != kBF16) return hipErrorInvalidValue;
         hipLaunchKernelGGL((k_head_gemm<kBF16, kRingShallow, true>), grid, block, 0, s, a);
     } else if (a.two_per_cu) {

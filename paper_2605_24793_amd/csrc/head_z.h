@@ -69,13 +69,13 @@ __device__ inline float head_z_cols(const HeadArgs &a, int64_t m, int lane, int 
                     const int kc = min(k0 + k, ksplit - 1);
                     u[i][k] = __builtin_nontemporal_load(&a.upart[(static_cast<int64_t>(kc) * a.m_cap + m) * a.h + nc]);
                 }
-            if constexpr (GROUPS) {   // groups of slices first (at most kHeadTileSlices slices, whole groups)
+            if constexpr (GROUPS) {   // groups of slices first: whole groups in a pass (zgroup <= SPL)
 #pragma unroll
                 for (int i = 0; i < CPL; ++i) {
                     float g = 0.f;
 #pragma unroll
-                    for (int k = 0; k < (SPL < kHeadTileSlices ? SPL : kHeadTileSlices); ++k) {
-                        g += u[i][k];
+                    for (int k = 0; k < SPL; ++k) {
+                        g += k0 + k < ksplit ? u[i][k] : 0.f;
                         if (((k + 1) & (a.zgroup - 1)) == 0) { v[i] += g; g = 0.f; }
                     }
                 }
@@ -112,7 +112,7 @@ __device__ inline float head_z(const HeadArgs &a, int64_t m, int64_t e, int lane
     float acc;
     if (FORM == kFew && ksplit <= 4)
         acc = a.h <= 256 ? head_z_cols<DT, 4, 4, false>(a, m, lane, ksplit) : head_z_cols<DT, 8, 4, false>(a, m, lane, ksplit);
-    else if (G)   // eight slices
+    else if (G)   // eight or sixteen slices, groups of at most eight
         acc = a.h <= 256 ? head_z_cols<DT, 4, 8, G>(a, m, lane, ksplit) : head_z_cols<DT, 8, 8, G>(a, m, lane, ksplit);
     else
         acc = a.h <= 256 ? head_z_cols<DT, 4, 16, G>(a, m, lane, ksplit) : head_z_cols<DT, 8, 8, G>(a, m, lane, ksplit);

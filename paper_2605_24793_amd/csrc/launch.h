@@ -18,7 +18,7 @@ constexpr int kHeadTargetBlocks = 128;
 constexpr int kHeadMaxSplit = 32;
 constexpr int kHeadMostBlocks = 512;  // cospec_arbitrate: no more workgroups than two per CU
 constexpr int kHeadSmallTile = 64;    // the tiles of the first layer beside the reduction
-constexpr int kHeadTileSlices = 8;    // ... and the slices of d they sum by themselves
+constexpr int kHeadTileGroups = 8;    // ... and the most groups of slices of d their workgroups share out
 constexpr int kXcds = 8;             // MI355X: 8 XCDs, each with its own L2
 constexpr int kMaxSeqRows = 256;      // rows per sequence / nodes per tree held in LDS
 constexpr int kSegVecs = 64;          // 16-byte vectors per probability-mass segment (one wave load)
@@ -140,11 +140,11 @@ struct HeadArgs {
     int32_t d, h;
     int32_t ksplit;            // slices of d, one workgroup each (head_ksplit); the
                                // persistent form may use fewer (headz::live_ksplit)
-    // The first layer in tiles beside the reduction (tile_gemm.h; else 0, 0): the
-    // kHeadTileSlices slices of d that one workgroup sums, and how many consecutive stored
-    // slices the second layer sums before it adds them up (powers of two).
-    int32_t kgroup, zgroup;
-    int32_t kslices;           // cospec_arbitrate: slices of d when a workgroup sums kgroup of them; else 0
+    // Slices of d that are each summed by themselves, the consecutive ones a workgroup takes
+    // (adding their sums in order) and the consecutive stored ones the second layer adds before
+    // it adds them up (powers of two): the first layer in tiles (tile_gemm.h), and
+    // cospec_arbitrate with kgroup > 1; else 0, 0, 0.
+    int32_t kslices, kgroup, zgroup;
     int32_t grid;              // chains: workgroups of the persistent GEMM (at most one per
                                // resident slot); 0: one workgroup per (tile, k-slice)
     int32_t two_per_cu;        // use the shallow LDS ring: two workgroups fit on a CU

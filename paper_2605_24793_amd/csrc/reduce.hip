@@ -725,7 +725,7 @@ hipError_t launch_reduce_head(Dtype dt, Dtype hdt, const ReduceArgs &a, const He
 }
 
 hipError_t launch_reduce_tiles(Dtype dt, const ReduceArgs &a, const HeadArgs &h, hipStream_t s) {
-    if (h.m_cap <= 0 || h.m_cap > slotgemm::kMaxSlots || h.ksplit < 1 || h.ksplit * h.kgroup != kHeadTileSlices)
+    if (h.m_cap <= 0 || h.m_cap > slotgemm::kMaxSlots || h.kslices < 1 || h.ksplit * h.kgroup != h.kslices)
         return hipErrorInvalidValue;
     const int64_t hb = tilegemm::blocks(h);
     const int64_t units = static_cast<int64_t>(a.n_rows) * a.plan.splits;

@@ -13,11 +13,14 @@
 //
 // A workgroup of four waves takes a 64 x 64 tile of U over part of d: 64-byte k-steps of 64
 // gathered hidden rows and 64 W1 rows go straight into an LDS ring, and each wave
-// accumulates 32 x 32 (v_mfma_f32_32x32x16_bf16).  d is cut into kSlices slices, each summed
+// accumulates 32 x 32 (v_mfma_f32_32x32x16_bf16).  d is cut into a.kslices slices, each summed
 // by itself; a workgroup runs a.kgroup of them and adds their sums in order, and where it runs
 // one the second layer adds them in the same groups (HeadArgs::zgroup).  So z is the same bits
-// in both forms.  Workgroups of one slice group stay on the same XCDs (the groups, 1, 2, 4 or
-// 8 of them, are dealt with the workgroups), whose L2 then reads that part of the operands.
+// in both forms.  The slices are as many as the tiled GEMM and the slot GEMM take at the same
+// sizes (8, 16 or 32): with 8 throughout, the relative error of z grew where those take more
+// (120 slots, 4096 -> 256: 1.0e-7 -> 1.4e-7).  Workgroups of one slice group stay on the same
+// XCDs (the groups, 2, 4 or 8 of them, are dealt with the workgroups), whose L2 then reads
+// that part of the operands.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -68,8 +71,10 @@ __device__ inline void run(const HeadArgs &a, int w, char *lds, const u32x4 *zer
     const int row_tiles = (m_cap + kTile - 1) / kTile;
     const int ks = w % a.ksplit, t = w / a.ksplit;
     const int s0 = t % row_tiles * kTile, n0 = t / row_tiles * kTile;
-    // a slice is whole 128-byte pieces of a row: an even number of stages
-    const int kslice = ((a.d + kHeadTileSlices - 1) / kHeadTileSlices + 2 * KE - 1) / (2 * KE) * (2 * KE);
+    // a slice is whole stages (whole 128-byte pieces left the workgroups of 5120 elements in 32
+    // slices 768 elements each, the last ones none: two trees of 38 nodes 26.1 us instead of
+    // 24.8)
+    const int kslice = ((a.d + a.kslices - 1) / a.kslices + KE - 1) / KE * KE;
     const int k0 = ks * a.kgroup * kslice, k1 = min(a.d, k0 + a.kgroup * kslice);
     const int nst = k1 > k0 ? (k1 - k0 + KE - 1) / KE : 0, slice_st = kslice / KE;
 

@@ -1162,6 +1162,27 @@ def test_split_t1_first_phase_outputs(B, K, V):
     assert not first["delta"][0, 0] and torch.isnan(first["logp_tgt"][-1, -1])
 
 
+def test_chain_head_tiles_error():
+    # 256 slots, 5120 -> 512: the tiles sum sixteen slices of d by themselves, as many as
+    # cospec_arbitrate does on as many rows, and are as exact (with eight slices the error was 1.19
+    # times as large; 4096 logits tell within 2%)
+    B, K, V, d, h = 32, 8, 512, 5120, 512
+    g = torch.Generator(device=DEV).manual_seed(5)
+    rnd = lambda *s: torch.randn(*s, generator=g, device=DEV)  # noqa: E731
+    tok = torch.zeros(B, K, dtype=torch.int32, device=DEV)
+    tgt, drf = (rnd(B, n, V).bfloat16() for n in (K + 1, K))
+    tgt[:, :, 1] = 100.0                                        # never the draft token: every slot is scored
+    e = {"tiles": 0.0, "rows": 0.0}
+    for _ in range(16):
+        hid = rnd(B, K, d).bfloat16()
+        head = workloads.Head((rnd(h, d) / d ** 0.5).bfloat16(), None, (rnd(h) / h ** 0.5).bfloat16(), 0.0)
+        ref = (hid.view(-1, d).double() @ head.w1.double().t().contiguous()).clamp(min=0) @ head.w2.double()
+        z = cs.verify_block(tgt, drf, tok, hid, head, 0.5)["z_tilde"].view(-1).double()
+        e["tiles"] += (z - ref).square().sum().item()
+        e["rows"] += (cs.arbitrate(hid.view(-1, d), head, 0.5)["z"].double() - ref).square().sum().item()
+    assert e["tiles"] <= 1.08 ** 2 * e["rows"]
+
+
 @pytest.mark.parametrize("B,N,d,h,V,shape", [
     (3, 20, 512, 65, 4097, "random"),      # 60 nodes, one column past a tile
     (2, 33, 456, 128, 20001, "star"),      # 66 nodes, a last slice of eight elements, leaves' draft rows unread
