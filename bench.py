@@ -223,13 +223,6 @@ def _conv(torch, bf16_bits, t):
     return bf16_bits(t) if t.dtype == torch.bfloat16 else t.contiguous().numpy()
 
 
-def head_in_tiles(slots, d, h):
-    """Whether the library runs a bf16 head's first layer in tiles in the reduction's launch
-    (head_tile_groups in paper_2605_24793_amd/csrc/cospec_api.hip)."""
-    tiles = -(-slots // 64) * -(-h // 64)
-    return slots >= 49 and tiles <= 128 and 449 <= d and slots * d * 2 <= 12 << 20
-
-
 class Step:
     """One workload resident on the GPU with its pre-marshalled verify call."""
 
@@ -266,9 +259,8 @@ class Step:
             # the library runs the head's first layer over every decision slot in the
             # reduction's launch: the timed launch holds both
             self.kernel = "k_vocab_reduce_head (reduction + the head's first layer on every slot)"
-        slots = wl.B * (wl.N if self.tree else wl.K)
-        if sps_u is None and wl.head.w1.dtype == torch.bfloat16 and head_in_tiles(
-                slots, wl.head.d, wl.head.h):
+        if sps_u is None and cs.binding.head_tile_groups(self.tree, wl.B, wl.N if self.tree else wl.K, wl.V,
+                                                         tgt.dtype, head):
             self.kernel = "k_vocab_reduce_tiles (reduction + the head's first layer in tiles)"
         self.logit_bytes = self.reduced_rows * wl.V * self.elem   # algorithmic bytes of the reductions
         self.step = self.p.launch

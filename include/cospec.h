@@ -160,11 +160,10 @@ typedef struct {
  * (verification tokens, Delta, mismatch list; for chains taken inside the head
  * GEMM, which derives its list, and the finish), (3) the head on the mismatch
  * rows, (4) finish (draft statistics, log p_D, verdicts, first stop, emission).
- * Chain batches of at most 256 decision slots, and with a bf16 head chain and tree
- * batches whose pre-activations fill at most 128 tiles of 64 slots x 64 columns and
- * whose hidden states are at most 12 MiB, run the head's first layer on every slot
- * inside the reduction's launch instead, and only the mismatches' logits are kept
- * (the reduce events then bracket that launch).
+ * Chain batches of at most 256 decision slots, and the chain and tree batches for which
+ * cospec_head_tile_groups is not 0, run the head's first layer on every slot inside the
+ * reduction's launch instead, and only the mismatches' logits are kept (the reduce events
+ * then bracket that launch).
  */
 typedef struct {
     hipEvent_t reduce_begin;  /* if non-NULL, recorded on `stream` just before ...        */
@@ -449,6 +448,16 @@ cospec_status cospec_hybrid_attention_ws(const void *q, const void *k, const voi
                                          const int32_t *q_start, int32_t B, int32_t n_q, int32_t L, int32_t Hq,
                                          int32_t Hkv, int32_t D, int32_t K, float scale, void *out,
                                          void *workspace, size_t workspace_bytes, hipStream_t stream);
+
+/*
+ * How a whole step of these sizes runs its head's first layer (n: draft tokens K of a chain,
+ * nodes N of a tree): in 64 x 64 tiles over every decision slot beside the reduction, each
+ * tile's sum over d shared out to the returned number of workgroups (2, 4 or 8); 0: not in
+ * tiles, or invalid sizes.  Tiles take a bf16 head of d >= 449 and 49 or more slots, while they
+ * are few enough to hide behind the reduction.
+ */
+int32_t cospec_head_tile_groups(int32_t is_tree, int32_t B, int32_t n, int32_t V, cospec_dtype logit_dtype,
+                                const cospec_head *head);
 
 /* Workspace bytes cospec_arbitrate needs (0 for invalid sizes). */
 size_t cospec_arbitrate_workspace_size(int64_t n_sel, const cospec_head *head);

@@ -130,6 +130,8 @@ def lib():
         L.cospec_hybrid_attention_ws.restype = I32
         L.cospec_hybrid_attention_ws.argtypes = [P, P, P, P, P, I32, I32, I32, I32, I32, I32, I32,
                                                  ctypes.c_float, P, P, SZ, P]
+        L.cospec_head_tile_groups.restype = I32
+        L.cospec_head_tile_groups.argtypes = [I32, I32, I32, I32, I32, HP]
         L.cospec_arbitrate.restype = I32
         L.cospec_arbitrate.argtypes = [P, I64, P, I64, HP, ctypes.c_float, P, P, P, SZ, P]
         _lib = L
@@ -164,6 +166,14 @@ def _head_struct(head) -> _Head:
             raise ValueError("head weights must be contiguous device tensors")
     return _Head(int(w1.shape[1]), int(w1.shape[0]), _dtype_code(w1), _ptr(w1), _ptr(b1),
                  _ptr(w2), float(b2))
+
+
+def head_tile_groups(is_tree: bool, B: int, n: int, V: int, logit_dtype: torch.dtype, head) -> int:
+    """How many workgroups share a tile of the head's first layer beside the reduction of a
+    whole step (n: draft tokens of a chain, nodes of a tree); 0: not in tiles."""
+    return lib().cospec_head_tile_groups(int(is_tree), int(B), int(n), int(V),
+                                         _BF16 if logit_dtype == torch.bfloat16 else _F32,
+                                         ctypes.byref(_head_struct(head)))
 
 
 def _row_stride(t: torch.Tensor) -> int:

@@ -90,10 +90,10 @@ inline size_t head_bytes(int64_t m_cap, const cospec_head *hd) {
 }
 
 // Steps whose head's first layer runs in tiles over every decision slot, beside the reduction
-// of `logit_bytes` (tile_gemm.h): the slice groups a tile's workgroups share out (1, 2, 4 or 8;
+// of `logit_bytes` (tile_gemm.h): the slice groups a tile's workgroups share out (2, 4 or 8;
 // 0: not in tiles).  bf16 heads only.
 //  - As many groups as keep the tiles' workgroups at one per CU: more displace the reduction
-//    (64 x K=7, 28 tiles: 54.4 us with 4 groups, 55.6 with 8, 61.8 with 2, 65.4 on the mismatch
+//    (64 x K=7, 28 tiles: 55.6 us with 8 groups, 54.4 with 4, 61.8 with 2, 65.4 on the mismatch
 //    rows after the reduction; 48 x K=10, 5120 -> 512, 64 tiles: 56.2 with 4, 61.1 with 8, 69.0
 //    after; 128 x K=7, 5120 -> 512, 112 tiles: 104.3 with 2, 110.2 with 4, 115.8 after).
 //  - More while they would outlast the reduction, at about 0.8 us a stage of 32 elements of
@@ -104,6 +104,12 @@ inline size_t head_bytes(int64_t m_cap, const cospec_head *hd) {
 //    nodes, 4096 -> 256, 240 tiles, 31 MB: repeated passes 299.1 -> 294.9 us, a first one 336 ->
 //    360; 32 such trees, 120 tiles, 16 MB: 173.6 -> 165.3, but 186 -> 199; 128 x K=7, 5120 ->
 //    512, 9 MB: 115.8 -> 104.3 and 136 -> 124).
+//  - Not where the tiles are many and long and the reduction too short to hide them: with the
+//    whole device they take about 0.95 ns a stage.  Few mismatches then cost less after the
+//    reduction (5120 -> 512, 3% mismatches, tiles against mismatch rows: 768 slots, 15360
+//    stages, V=16000 31.5 and 33.0 us; 896 slots V=16000 37.2 and 32.6, V=32000 44.4 and 43.0,
+//    V=128256 93.2 and 100.6; 1024 slots V=64000 73.7 and 69.8, V=128256 105.9 and 113.7; 16
+//    trees of 60 nodes, V=128256 93.2 and 90.3).
 int32_t head_tile_groups(int64_t m_cap, const cospec_head *hd, int64_t logit_bytes) {
     constexpr int64_t kCus = 256, kMostHidden = 12 << 20;
     if (hd->dtype != COSPEC_BF16 || m_cap < kTilesMinSlots) return 0;
@@ -111,6 +117,8 @@ int32_t head_tile_groups(int64_t m_cap, const cospec_head *hd, int64_t logit_byt
     // at least eight slices, and a place for their partials in the form on its own
     if (2 * tiles > kCus || m_cap * hd->d * 2 > kMostHidden || ksplit_for(m_cap, hd) < kHeadTileGroups) return 0;
     const double reduce_us = static_cast<double>(logit_bytes) / 6.5e6, tile_us = hd->d / 32 * 0.8;
+    const int64_t stages = tiles * (hd->d / 32);
+    if (stages > 16000 && reduce_us < 4 * 0.95e-3 * stages) return 0;
     int32_t groups = kHeadTileGroups;
     while (tiles * groups > kCus) groups /= 2;
     while (groups < kHeadTileGroups && tile_us > groups * reduce_us) groups *= 2;
@@ -251,9 +259,11 @@ struct Common {
     hipStream_t stream;
 };
 
-// Logit bytes the step's reduction reads (trees: about half of the draft rows have a child).
-int64_t step_logit_bytes(const Common &c) {
-    return static_cast<int64_t>(c.B) * (c.RT + (c.is_tree ? c.RD / 2 : c.RD)) * c.V * elem_bytes(c.dt);
+// head_tile_groups of a step; its reduction reads, of trees, about half of the draft rows (those
+// of nodes with a child).
+int32_t step_tile_groups(const Common &c) {
+    const int64_t bytes = static_cast<int64_t>(c.B) * (c.RT + (c.is_tree ? c.RD / 2 : c.RD)) * c.V * elem_bytes(c.dt);
+    return head_tile_groups(static_cast<int64_t>(c.B) * c.D, c.head, bytes);
 }
 
 // Which part of the step a call enqueues: the whole step, or one of the two
@@ -273,8 +283,7 @@ cospec_status run(const Common &c, Phase phase, int32_t *accept_len, int32_t *ou
     }
     const Layout L = layout(rows, c.B, c.RT, c.D, c.head, c.V);
     const float *uniform = c.opts ? c.opts->sample_uniform : nullptr;
-    const bool head_beside =
-        !c.is_tree && c.D > 0 && head_tile_groups(static_cast<int64_t>(c.B) * c.D, c.head, step_logit_bytes(c)) > 0;
+    const bool head_beside = !c.is_tree && c.D > 0 && step_tile_groups(c) > 0;
     const PartPlan plan = make_plan(n_tgt, n_drf, nvec, override_splits, static_cast<Dtype>(c.dt), head_beside);
     if (uniform && !aligned(uniform, 4)) return COSPEC_ERR_INVALID_ARG;
     const float *policy_u = c.opts ? c.opts->policy_uniform : nullptr;
@@ -329,7 +338,7 @@ cospec_status run(const Common &c, Phase phase, int32_t *accept_len, int32_t *ou
     // the reduction's launch for a whole step and on its own in the second phase of a
     // split one, instead of on the mismatch rows after the reduction (both forms of the
     // step then compute z alike)
-    const int32_t tile_groups = head ? head_tile_groups(m_cap, c.head, step_logit_bytes(c)) : 0;
+    const int32_t tile_groups = head ? step_tile_groups(c) : 0;
     const bool tiles = tile_groups > 0 && phase != kReducePhase;
     const bool every_slot = fuse_head && phase != kReducePhase && (tiles || m_cap <= kEverySlotMax);
     HeadArgs ha{};
@@ -600,6 +609,17 @@ size_t cospec_verify_block_workspace_size(int32_t B, int32_t K, int32_t V, const
 size_t cospec_verify_tree_workspace_size(int32_t B, int32_t N, int32_t V, const cospec_head *head) {
     if (B < 0 || N < 1 || N > COSPEC_MAX_N || V < 1 || check_head(head) != COSPEC_OK) return 0;
     return layout(static_cast<int64_t>(B) * 2 * N, B, N, N, head, V).total;
+}
+
+int32_t cospec_head_tile_groups(int32_t is_tree, int32_t B, int32_t n, int32_t V, cospec_dtype logit_dtype,
+                                const cospec_head *head) {
+    if (B < 1 || n < 1 || n > (is_tree ? COSPEC_MAX_N : COSPEC_MAX_K) || V < 1 || !dtype_ok(logit_dtype) ||
+        check_head(head) != COSPEC_OK)
+        return 0;
+    Common c{};
+    c.dt = logit_dtype; c.head = head; c.B = B; c.V = V; c.is_tree = is_tree != 0;
+    c.RT = is_tree ? n : n + 1; c.RD = c.D = n;
+    return step_tile_groups(c);
 }
 
 // Host-side checks of a chain call; fills `c` on success.

@@ -314,6 +314,25 @@ def test_static_scratch_entry_point_rejects_before_any_launch():
     assert "static buffer" in binding.status_string(-5)
 
 
+@pytest.mark.parametrize("tree,B,n,V,d,h,groups", [
+    (0, 64, 7, 151936, 4096, 256, 8),      # 28 tiles
+    (0, 48, 25, 128256, 4096, 256, 2),     # 76 tiles: two groups stay at one workgroup per CU
+    (0, 128, 7, 151936, 5120, 512, 2),     # 112 long tiles behind 90 us of reduction
+    (0, 128, 7, 16000, 5120, 512, 0),      # ... and behind 9 us: they would outlast it
+    (0, 256, 4, 64000, 5120, 512, 0), (0, 256, 4, 128256, 5120, 512, 2),
+    (0, 96, 8, 16000, 5120, 512, 8),       # 96 tiles are short enough anywhere
+    (1, 16, 60, 128256, 5120, 512, 0), (1, 12, 60, 128256, 5120, 512, 4),
+    (0, 6, 8, 32000, 4096, 256, 0), (0, 7, 7, 32000, 4096, 256, 8),          # 48 and 49 slots
+    (0, 7, 7, 32000, 448, 256, 0), (0, 7, 7, 32000, 456, 256, 8),            # seven and eight stages of d
+    (0, 256, 7, 151936, 5120, 512, 0),     # 18 MB of hidden states
+    (0, 0, 7, 32000, 4096, 256, 0), (0, 7, 65, 32000, 4096, 256, 0), (1, 1, 257, 32000, 4096, 256, 0),
+])
+def test_head_tile_groups(tree, B, n, V, d, h, groups):
+    L = cs.lib()
+    assert L.cospec_head_tile_groups(tree, B, n, V, 1, ctypes.byref(_head(d=d, h=h))) == groups
+    assert L.cospec_head_tile_groups(tree, B, n, V, 1, ctypes.byref(_head(d=d, h=h, dtype=0))) == 0
+
+
 def test_bench_names_the_launch_the_library_takes():
     # bench.py labels the timed launch of chain batches of at most EVERY_SLOT_MAX decision
     # slots as the reduction with the head's first layer; the library's limit must agree
