@@ -732,6 +732,13 @@ constexpr int64_t kMinChunk = 128;    // keys of a piece, at least
 // a call of two launches takes 13.5 us at the least (8 groups, D = 128: 417 keys 13.0 uncut, 537
 // keys 15.1 uncut and 13.5 cut; D = 64: 537 keys 11.9 uncut, 717 15.1).  More groups than CUs are
 // not cut: two of them already share a CU.
+// From kWideMinRows rows on the uncut call runs the wide kernel, whose time with at most one
+// workgroup per CU is a line in L (212 to 1048 rows, within 0.6 us: D = 128 16.6 us at 653 keys,
+// 39.3 at 2053, 104.7 at 6083; D = 64 11.7, 27.7 and 73.0), and a cut must win by what its cost
+// falls short of there.  64 calls of 129 rows or more, uncut and cut: one input of 2017
+// positions, 16/8 heads, D = 64 27.0 and 46.2 us, 8/8 heads, D = 128 38.4 and 38.2, 1217 positions 25.3
+// and 22.9; 4 x 1083 keys, 332 rows, D = 64 16.3 and 21.0; 2 x 6083 keys 73.6 and 28.2; the rule takes
+// the slower one twice, by 0.4 and 0.8 us.
 AttnPlan attn_plan(int32_t B, int32_t n_q, int32_t L, int32_t Hq, int32_t Hkv, int32_t D) {
     AttnPlan p{1, 0, 0};
     const int64_t rows = static_cast<int64_t>(n_q) * (Hq / Hkv);
@@ -741,8 +748,9 @@ AttnPlan attn_plan(int32_t B, int32_t n_q, int32_t L, int32_t Hq, int32_t Hkv, i
     if (wgs > kCus) return p;
     const double t1 = D == 128 ? 0.023 : 0.0185, t2 = D == 128 ? 0.037 : 0.022;
     const double piece_us = static_cast<double>(std::min<int64_t>(rows, 16 * waves)) * D * 8 / 3e6;
-    double best = L * t1;
-    if (best < 10.5) return p;
+    const bool wide = rows >= kWideMinRows;
+    double best = !wide ? L * t1 : D == 128 ? 5.8 + 0.01625 * L - 1.0 : 4.6 + 0.01125 * L - 2.7;
+    if (best < (wide ? 13.7 : 10.5)) return p;
     for (int64_t s = 2; s <= 64 && wgs * s <= 2 * kCus; ++s) {
         const int64_t chunk = ((L + s - 1) / s + kKeyBlock - 1) / kKeyBlock * kKeyBlock;
         if (chunk < kMinChunk) break;

@@ -250,6 +250,10 @@ def test_hybrid_attention_workspace():
     assert size(64, 17, 2065, 32, 8, 128) == 0     # more groups than CUs: not cut
     assert size(2, 17, 100, 8, 2, 128) == 0        # too short to cut
     assert size(0, 17, 4096, 8, 2, 128) == 0 and size(2, 0, 4096, 8, 2, 128) == 0
+    # more than 128 rows per group: cut only where that beats the wide kernel
+    assert size(1, 2017, 2017, 16, 8, 64) == 0 and size(1, 717, 717, 8, 8, 64) == 0
+    assert size(4, 83, 1083, 32, 8, 64) == 0 and size(2, 83, 6083, 32, 8, 64) > 0
+    assert size(1, 53, 653, 32, 8, 128) > 0 and size(1, 53, 653, 32, 8, 64) == 0
     for bad in ((-1, 17, 100, 8, 2, 128), (2, 17, 100, 6, 4, 128), (2, 17, 100, 8, 2, 96)):
         assert size(*bad) == 0
 
