@@ -215,10 +215,14 @@ int64_t split_vectors(int64_t nvec, int32_t splits, bool segments) {
 }
 
 // The partial layout of a step: the caller's split count, or the rule above.  Both
-// phases of a split step derive it from the same arguments.  head_beside: the head's tiles may
-// run beside the reduction; they hold some of the device's places throughout, so that whole
-// rows would end in an uneven last round (256 x K=7, 4096 -> 256, with its head in tiles: 195.1 us
-// in whole rows, 192 in two pieces, 190.6 in four).
+// phases of a split step derive it from the same arguments.  head_beside: the head's tiles
+// run beside the reduction (or, in a split step, may run after it: both forms of a step cut
+// their rows alike).  They hold some of the device's places throughout, so that whole rows end
+// in an uneven last round: rows of at least 8 vectors per lane and piece are cut into four
+// (256 x K=6, 4096 -> 256, V=151936: 165.5 us in whole rows, 163.4 in two pieces, 161.7 in four;
+// 240 x K=6, V=65000 85.5 -> 80.8; 220 x K=7, 2048 -> 256, V=128256 143.0 -> 141.4; split steps
+// 256 x K=7, V=128256 186.5 -> 182.7; but shorter rows lose: 220 x K=7, V=50001 69.6 -> 71.0, and
+// so does a step that runs no head: 256 x K=6 161.3 -> 163.5).
 PartPlan make_plan(int64_t n_tgt_rows, int64_t n_drf_rows, int64_t nvec, int32_t override_splits, Dtype dt,
                    bool head_beside) {
     PartPlan p{};
@@ -226,7 +230,7 @@ PartPlan make_plan(int64_t n_tgt_rows, int64_t n_drf_rows, int64_t nvec, int32_t
     const int64_t rows = n_tgt_rows + n_drf_rows;
     p.splits = override_splits > 0 ? override_splits : auto_splits(rows, nvec, reduce_slots(dt));
     if (override_splits == 0 && head_beside && p.splits == 1 && rows <= kMaxReduceSlots &&
-        nvec >= 4 * 4 * kReduceThreads)
+        nvec >= 4 * 8 * kReduceThreads)
         p.splits = 4;
     return p;
 }
@@ -283,10 +287,16 @@ cospec_status run(const Common &c, Phase phase, int32_t *accept_len, int32_t *ou
     }
     const Layout L = layout(rows, c.B, c.RT, c.D, c.head, c.V);
     const float *uniform = c.opts ? c.opts->sample_uniform : nullptr;
-    const bool head_beside = !c.is_tree && c.D > 0 && step_tile_groups(c) > 0;
+    const float *policy_u = c.opts ? c.opts->policy_uniform : nullptr;
+    const cospec_features F = c.feats ? *c.feats : cospec_features{};
+    const bool decisions = c.B > 0 && (c.is_tree ? c.D > 1 : c.D > 0);
+    const bool lambda_decides = !(c.lambda >= 0.0f && c.lambda < 1.0f);
+    const bool want_scores = F.z_tilde || F.policy || F.logp_action;
+    const bool head = decisions && (!lambda_decides || want_scores || policy_u);
+    // a split step's first phase does not know whether the second runs the head
+    const bool head_beside = !c.is_tree && (phase == kWhole ? head : decisions) && step_tile_groups(c) > 0;
     const PartPlan plan = make_plan(n_tgt, n_drf, nvec, override_splits, static_cast<Dtype>(c.dt), head_beside);
     if (uniform && !aligned(uniform, 4)) return COSPEC_ERR_INVALID_ARG;
-    const float *policy_u = c.opts ? c.opts->policy_uniform : nullptr;
     if (policy_u && !aligned(policy_u, 4)) return COSPEC_ERR_INVALID_ARG;
     const cospec_rl *rl = c.opts ? c.opts->rl : nullptr;
     if (rl) {
@@ -315,11 +325,6 @@ cospec_status run(const Common &c, Phase phase, int32_t *accept_len, int32_t *ou
     float *zlog = reinterpret_cast<float *>(ws + L.z);
     float *xtok = reinterpret_cast<float *>(ws + L.xtok);
 
-    const cospec_features F = c.feats ? *c.feats : cospec_features{};
-    const bool decisions = c.B > 0 && (c.is_tree ? c.D > 1 : c.D > 0);
-    const bool lambda_decides = !(c.lambda >= 0.0f && c.lambda < 1.0f);
-    const bool want_scores = F.z_tilde || F.policy || F.logp_action;
-    const bool head = decisions && (!lambda_decides || want_scores || policy_u);
     const bool do_reduce = phase != kArbitratePhase, do_arbitrate = phase != kReducePhase;
     // chains: the head GEMM's workgroups derive the mismatch list from the partials
     const bool build_list = !c.is_tree && static_cast<int64_t>(c.B) * c.D <= kBuildListMax;

@@ -1162,6 +1162,36 @@ def test_split_t1_first_phase_outputs(B, K, V):
     assert not first["delta"][0, 0] and torch.isnan(first["logp_tgt"][-1, -1])
 
 
+def test_rows_in_four_pieces_beside_the_tiles():
+    # 3072 rows of 65536 elements with the head's tiles beside them: the rows are cut into four
+    # pieces, in the phases of a split step too; a step that runs no head, and rows one 256-byte
+    # block shorter, stay whole
+    B, K, d, h = 1024, 1, 456, 64
+    g = torch.Generator(device=DEV).manual_seed(6)
+    rnd = lambda *s: torch.randn(*s, generator=g, device=DEV)  # noqa: E731
+    head = workloads.Head((rnd(h, d) / d ** 0.5).bfloat16(), None, (rnd(h) / h ** 0.5).bfloat16(), 0.0)
+    hid, stats = rnd(B, K, d).bfloat16(), ["tgt_lse", "tgt_entropy", "drf_lse", "drf_entropy"]
+    tok = torch.randint(0, 65536, (B, K), generator=g, device=DEV, dtype=torch.int32)
+    full = [(rnd(B, n, 65536) * 4).bfloat16() for n in (K + 1, K)]
+    for V, no_head, pieces in ((65536, False, 4), (65536, True, 1), (65408, False, 1)):
+        tgt, drf = (x[:, :, :V] for x in full)
+        assert cs.binding.head_tile_groups(False, B, K, V, tgt.dtype, head) > 0
+
+        def step(splits):
+            p = cs.prepare_block(tgt, drf, tok, hid, head, 1.5 if no_head else 0.5, splits=splits)
+            if no_head:                                     # lambda decides and no score is asked for
+                p._feats.z_tilde = p._feats.policy = p._feats.logp_action = None
+            p.launch()
+            torch.cuda.synchronize()
+            return p.result()
+        auto, same, other = step(0), step(pieces), step(5 - pieces)
+        _same(auto, same, stats + ["accept_len", "tokens", "logp_tgt", "logp_drf"])
+        assert not torch.equal(auto["tgt_lse"], other["tgt_lse"])
+        if not no_head:
+            split = cs.SplitBlock(tgt, drf, tok, head).arbitrate(hid, 0.5)
+            _same(auto, split, list(auto))
+
+
 def test_chain_head_tiles_error():
     # 256 slots, 5120 -> 512: the tiles sum sixteen slices of d by themselves, as many as
     # cospec_arbitrate does on as many rows, and are as exact (with eight slices the error was 1.19
