@@ -483,8 +483,8 @@ cospec_status run(const Common &c, Phase phase, int32_t *accept_len, int32_t *ou
         // step (whose outputs, the candidates, the caller needs before phase 2); in a
         // whole chain step the finish takes it, and the head GEMM derives its list
         // itself, unless the batch has more decision slots than the GEMM's workgroups
-        // list (then this kernel builds the list the GEMM reads)
-        if (c.is_tree || (phase == kReducePhase && !sample_decides) || (head && !build_list)) {
+        // list (then this kernel builds the list the GEMM reads; in tiles nothing reads it)
+        if (c.is_tree || (phase == kReducePhase && !sample_decides) || (head && !build_list && !every_slot)) {
             if (launch_decide(dt, da, c.stream) != hipSuccess) return COSPEC_ERR_HIP;
         }
     }

@@ -1113,6 +1113,7 @@ def test_chain_finish_slots_per_wave(B, K, noise):
     (40, 12, 640, 600, "bf16", True, True),     # 8 x 10 tiles, h past whole tiles
     (60, 17, 512, 512, "bf16", False, False),   # 16 x 8 = 128 tiles, the most
     (61, 17, 512, 512, "bf16", False, False),   # 17 x 8: past them, on the mismatch rows
+    (700, 6, 456, 64, "bf16", True, False),     # 4200 slots: more than the head GEMM lists, no list in tiles
 ])
 def test_chain_head_tiles(B, K, d, h, ldt, packed, t1):
     # the head's first layer in 64 x 64 tiles over every decision slot: against the oracle, and
