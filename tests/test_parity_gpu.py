@@ -659,8 +659,7 @@ def _same(a, b, keys):
             assert torch.equal(x, y), k
 
 
-# 24 x 7 decision slots: the head's first layer runs on every slot (beside the
-# reduction, and on its own in phase 2); 80 x 7 = 560: on the mismatch rows only
+# the head's first layer runs in tiles over every slot, beside the reduction and on its own in phase 2
 @pytest.mark.parametrize("t1,B", [(False, 24), (True, 24), (False, 80)])
 def test_split_phases_equal_the_whole_step(t1, B):
     wl = workloads.make_config(3, B=B)
@@ -711,8 +710,8 @@ def test_packed_hidden_rows():
 
 @pytest.mark.parametrize("B", [16, 90])
 def test_packed_hidden_rows_whole_step(B):
-    # the whole step with packed hidden states (16 x 7 slots: first layer on every slot;
-    # 90 x 7 = 630: on the mismatch rows) equals the step on [B, K, d] bit for bit
+    # the whole step with packed hidden states (first layer in tiles over every slot) equals the
+    # step on [B, K, d] bit for bit
     wl = workloads.make_config(3, B=B)
     K, d = wl.K, wl.head.d
     g = torch.Generator().manual_seed(5)
@@ -1105,22 +1104,15 @@ def test_chain_finish_slots_per_wave(B, K, noise):
     parity.check_block(gpu, _ref_block(wl, 0.5))
 
 
-@pytest.mark.parametrize("B,K,d,h,ldt,packed,t1", [
-    (7, 7, 512, 65, "bf16", False, False),      # 49 slots, one column past a tile, slices of one piece
-    (16, 4, 520, 64, "bf16", True, False),      # one whole tile; d past four slices, three slices empty
-    (13, 5, 456, 128, "f32", False, False),     # 65 slots, a last slice of eight elements, fp32 logits
-    (41, 25, 1024, 256, "bf16", False, True),   # 17 x 4 tiles in two groups, temperature 1
-    (40, 12, 640, 600, "bf16", True, True),     # 8 x 10 tiles, h past whole tiles
-    (60, 17, 512, 512, "bf16", False, False),   # 16 x 8 = 128 tiles, the most
-    (61, 17, 512, 512, "bf16", False, False),   # 17 x 8: past them, on the mismatch rows
-    (700, 6, 456, 64, "bf16", True, False),     # 4200 slots: more than the head GEMM lists, no list in tiles
-])
-def test_chain_head_tiles(B, K, d, h, ldt, packed, t1):
-    # the head's first layer in 64 x 64 tiles over every decision slot: against the oracle, and
-    # the two phases of a split step bit for bit the whole step
-    wl = workloads.make_chain(B=B, K=K, V=3001, d=d, h=h, dtype="bf16", seed=B + K, bias=True, noise=1.2)
+def _phases_case(B, K, V, d, h, ldt, packed, t1, groups):
+    """The whole step against the oracle, and bit for bit against the two phases of a split
+    step; `groups`: how many workgroups share a tile of the head's first layer (0: not in tiles)."""
+    hdt = "f32" if ldt == "f32 head" else "bf16"
+    wl = workloads.make_chain(B=B, K=K, V=V, d=d, h=h, dtype=hdt, seed=B + K, bias=True, noise=1.2)
     if ldt == "f32":
         wl.target, wl.draft = wl.target.float(), wl.draft.float()
+    head = _head_dev(wl.head)
+    assert cs.binding.head_tile_groups(False, B, K, V, wl.target.dtype, head) == groups
     g = torch.Generator().manual_seed(7)
     u = torch.rand(B, K + 1, generator=g) if t1 else None
     hid, row0 = wl.hidden, None
@@ -1132,8 +1124,8 @@ def test_chain_head_tiles(B, K, d, h, ldt, packed, t1):
     tgt, drf, tok = _padded(wl.target, 7), _padded(wl.draft, 7), wl.draft_tokens.to(DEV)
     ud = None if u is None else u.to(DEV)
     r0 = None if row0 is None else row0.to(DEV)
-    whole = cs.verify_block(tgt, drf, tok, hid.to(DEV), _head_dev(wl.head), 0.4, sample_u=ud, hidden_row0=r0)
-    sb = cs.SplitBlock(tgt, drf, tok, _head_dev(wl.head), sample_u=ud)
+    whole = cs.verify_block(tgt, drf, tok, hid.to(DEV), head, 0.4, sample_u=ud, hidden_row0=r0)
+    sb = cs.SplitBlock(tgt, drf, tok, head, sample_u=ud)
     split = sb.arbitrate(hid.to(DEV), 0.4, hidden_row0=r0)
     torch.cuda.synchronize()
     for k, v in whole.items():
@@ -1142,6 +1134,49 @@ def test_chain_head_tiles(B, K, d, h, ldt, packed, t1):
     gpu = {k: v.cpu() for k, v in whole.items()}
     cand = gpu["tgt_candidate"].numpy() if t1 else None
     parity.check_block(gpu, _ref_block(wl, 0.4, u, cand))
+
+
+# A short vocabulary leaves the tiles nothing to hide behind: eight workgroups share each
+@pytest.mark.parametrize("B,K,d,h,ldt,packed,t1", [
+    (7, 7, 512, 65, "bf16", False, False),      # 49 slots, one column past a tile, slices of one piece
+    (16, 4, 520, 64, "bf16", True, False),      # one whole tile; d past five slices of 96, two empty
+    (13, 5, 456, 128, "f32", False, False),     # 65 slots, slices of 64 and a last one of eight elements, fp32 logits
+    (41, 25, 1024, 256, "bf16", False, True),   # 17 x 4 tiles, temperature 1
+    (40, 12, 640, 600, "bf16", True, True),     # 8 x 10 tiles, h past whole tiles
+    (60, 17, 512, 512, "bf16", False, False),   # 16 x 8 = 128 tiles, the most
+    (61, 17, 512, 512, "bf16", False, False),   # 17 x 8: past them, on the mismatch rows
+])
+def test_chain_head_tiles(B, K, d, h, ldt, packed, t1):
+    # the head's first layer in 64 x 64 tiles over every decision slot
+    _phases_case(B, K, 3001, d, h, ldt, packed, t1, 0 if B == 61 else 8)
+
+
+@pytest.mark.parametrize("B,K,V,d,h,packed,t1,groups", [
+    (41, 25, 10100, 512, 256, True, True, 2),    # 17 x 4 tiles, four slices a workgroup, temperature 1, packed rows
+    (41, 25, 10100, 512, 256, False, False, 2),
+    (40, 12, 26001, 640, 600, True, False, 2),   # 8 x 10 tiles, h past whole tiles
+    (60, 15, 5700, 520, 256, False, True, 4),    # 15 x 4, slices of 96 elements, one of 40 and two empty
+    (30, 10, 33100, 1024, 512, True, True, 4),   # 5 x 8, temperature 1, packed rows
+    (700, 6, 3001, 456, 64, True, False, 2),     # 4200 slots: more than the head GEMM lists, no list in tiles
+    (20, 7, 3001, 1032, 320, True, False, 8),    # sixteen slices in pairs, the last of 72 elements, h in two passes
+    (28, 9, 3001, 2048, 130, False, True, 8),    # sixteen slices, temperature 1
+])
+def test_chain_head_tiles_in_groups(B, K, V, d, h, packed, t1, groups):
+    # a workgroup sums several slices beside the reduction; in the phases the second layer does
+    _phases_case(B, K, V, d, h, "bf16", packed, t1, groups)
+
+
+@pytest.mark.parametrize("B,K,V,d,h,ldt,packed,t1", [
+    (4, 7, 5003, 512, 128, "bf16", False, False),      # 28 slots: the slot GEMM, in the reduction's launch and alone
+    (4, 7, 5003, 520, 40, "bf16", True, True),
+    (24, 7, 3001, 256, 70, "f32 head", False, True),   # fp32 heads: the slot GEMM to 256 slots
+    (24, 7, 3001, 260, 64, "f32 head", True, False),
+    (45, 7, 3001, 256, 128, "bf16", True, False),      # 315 slots of a short d: on the mismatch rows
+    (40, 8, 3001, 128, 300, "f32 head", True, True),   # ... and of an fp32 head
+    (80, 7, 3001, 5120, 1100, "bf16", True, False),    # 9 x 18 tiles: on the mismatch rows
+])
+def test_phases_not_in_tiles(B, K, V, d, h, ldt, packed, t1):
+    _phases_case(B, K, V, d, h, ldt, packed, t1, 0)
 
 
 @pytest.mark.parametrize("B,K,V", [(3, 1, 4097), (5, 7, 20001), (2, 64, 513)])
@@ -1214,15 +1249,18 @@ def test_chain_head_tiles_error():
     assert e["tiles"] <= 1.08 ** 2 * e["rows"]
 
 
-@pytest.mark.parametrize("B,N,d,h,V,shape", [
-    (3, 20, 512, 65, 4097, "random"),      # 60 nodes, one column past a tile
-    (2, 33, 456, 128, 20001, "star"),      # 66 nodes, a last slice of eight elements, leaves' draft rows unread
-    (9, 64, 1024, 256, 3001, "random"),    # 9 x 4 tiles exactly, 4 groups
-    (40, 30, 512, 512, 40001, "path"),     # 19 x 8 tiles: past them, on the mismatch nodes
-    (33, 30, 512, 512, 40001, "path"),     # 16 x 8 tiles, the most, 2 groups
+@pytest.mark.parametrize("B,N,d,h,V,shape,groups", [
+    (3, 20, 512, 65, 4097, "random", 8),      # 60 nodes, one column past a tile
+    (2, 33, 456, 128, 20001, "star", 8),      # 66 nodes, a last slice of eight elements, leaves' draft rows unread
+    (9, 64, 1024, 256, 3001, "random", 8),    # 9 x 4 tiles exactly
+    (9, 64, 1024, 256, 24101, "random", 4),
+    (4, 30, 2560, 300, 3001, "random", 8),    # 120 nodes: 32 slices, four a workgroup
+    (40, 30, 512, 512, 40001, "path", 0),     # 19 x 8 tiles: past them, on the mismatch nodes
+    (33, 30, 512, 512, 40001, "path", 2),     # 16 x 8 tiles, the most
 ])
-def test_tree_head_tiles(B, N, d, h, V, shape):
+def test_tree_head_tiles(B, N, d, h, V, shape, groups):
     # trees whose head's first layer runs in tiles over every node, the second on the listed mismatches
     tr = workloads.make_random_tree(B, N, V, d, h, dtype="bf16", noise=1.3, seed=B + N, bias=True, shape=shape)
+    assert cs.binding.head_tile_groups(True, B, N, V, tr.target.dtype, _head_dev(tr.head)) == groups
     gpu = _gpu_tree(tr, 0.45, pad=5)
     parity.check_tree(gpu, _ref_tree(tr, 0.45))
