@@ -4,17 +4,24 @@
 // verify_block / verify_tree enqueue, on the caller's stream:
 //   1. k_vocab_reduce   every target and draft row (tree: draft rows of nodes with
 //                       a child), one workgroup per (row, split) -> split partials
-//                       (max, argmax, S, T); zeroes the list counter
+//                       (max, argmax, S, T); zeroes the list counter.  With the head's
+//                       first layer over every decision slot in the same launch:
+//                       k_vocab_reduce_tiles (64 x 64 tiles, head_tile_groups below) or
+//                       k_vocab_reduce_head (the slot GEMM, small chain batches)
 //   1b. k_sample        temperature 1 only: one wave per target row samples the
 //                       candidate by inversion of its uniform (segment masses
-//                       written by step 1, then one segment re-read)
-//   2. k_decide         trees (and the first phase of a split chain step): one
-//                       workgroup per tree: target statistics, Delta, log p_T, mismatch
-//                       compaction (device-side count M)
+//                       written by step 1, then one segment re-read); in the first phase
+//                       of a split chain step it writes the decision step's outputs too
+//   2. k_decide         trees, the other first phases, and chains whose head GEMM cannot
+//                       list its rows itself: one workgroup per sequence: target
+//                       statistics, Delta, log p_T, mismatch compaction (device-side count M)
 //   3. k_head_gemm (+ k_head_epilogue for trees)   MFMA head over the M compacted
 //                       rows (skipped when the threshold decides every mismatch by
-//                       itself and no score is requested); for chains each workgroup
-//                       derives the mismatch list itself from the partials
+//                       itself and no score is requested, or when step 1 ran it; trees
+//                       in tiles keep the epilogue); for chains each workgroup derives the
+//                       mismatch list itself from the partials.  A split step's second
+//                       phase runs the tiles (k_tile_gemm) or the slot GEMM
+//                       (k_slot_gemm) here instead
 //   4. k_chain_finish(_head) / k_tree_finish   chains: the decision step (target
 //                       statistics, Delta, log p_T); draft statistics, log p_D, the
 //                       head's second layer (chains), verdicts (threshold or sampled),
@@ -55,9 +62,10 @@ constexpr int64_t kMaxRowBytes = INT32_MAX;    // V * element bytes of one logit
 // K=7 (448 slots) 65.6 us on the mismatch rows, 66.8 on every slot.
 constexpr int64_t kEverySlotMax = 256;
 constexpr int32_t kEverySlotSplits = 16;
-// From this many slots on, a bf16 head runs in 64 x 64 tiles there instead (tile_gemm.h): 16 x
-// K=4 (64 slots) 18.4 -> 17.4 us, 3 x K=20 (60) with h = 320 24.5 -> 17.3, but 8 x K=5 (40) 14.6 ->
-// 15.3 and 4 x K=7 (28) 17.8 -> 18.1.
+// From this many slots on, a bf16 head runs in 64 x 64 tiles there instead (tile_gemm.h), whatever
+// its size: 49 to 60 slots, V=32000, slot GEMM and tiles 11.9 and 11.2 us (512 -> 128), 13.0 and
+// 11.7 (2048 -> 256), 13.4 and 12.7 (4096 -> 256), 18.2 and 15.1 (5120 -> 512); but 8 x K=5 (40),
+// 4096 -> 256 14.6 and 15.3, 4 x K=7 (28) 17.8 and 18.1.
 constexpr int64_t kTilesMinSlots = 49;
 
 inline size_t round_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
