@@ -105,19 +105,21 @@ inline size_t head_bytes(int64_t m_cap, const cospec_head *hd) {
 //    rows after the reduction; 48 x K=10, 5120 -> 512, 64 tiles: 56.2 with 4, 61.1 with 8, 69.0
 //    after; 128 x K=7, 5120 -> 512, 112 tiles: 104.3 with 2, 110.2 with 4, 115.8 after).
 //  - More while they would outlast the reduction, at about 0.8 us a stage of 32 elements of
-//    d beside it against 6.5 TB/s (16 trees of 38 nodes, 5120 -> 512, 80 tiles, 245 MB: 68.3 with
-//    2 groups, 61.8 with 4, 67.2 after).
+//    d beside it against 6.5 TB/s, up to two workgroups per CU (16 trees of 38 nodes, 5120 -> 512,
+//    80 tiles, 245 MB: 68.3 with 2 groups, 61.8 with 4, 67.2 after; 26 trees of 60 nodes, 2560 ->
+//    320, 125 tiles, V=16000 45.0 with 8 groups, 41.0 with 4, 42.9 after; 192 x K=8, 4096 -> 256,
+//    V=16000 39.7, 33.7, 40.8).
 //  - Never one group (all of d), and no more than kMostHidden of hidden states: those tiles
 //    gain little and, on a first pass over new buffers, outlast the reduction (64 trees of 60
 //    nodes, 4096 -> 256, 240 tiles, 31 MB: repeated passes 299.1 -> 294.9 us, a first one 336 ->
 //    360; 32 such trees, 120 tiles, 16 MB: 173.6 -> 165.3, but 186 -> 199; 128 x K=7, 5120 ->
 //    512, 9 MB: 115.8 -> 104.3 and 136 -> 124).
-//  - Not where the tiles are many and long and the reduction too short to hide them: with the
-//    whole device they take about 0.95 ns a stage.  Few mismatches then cost less after the
-//    reduction (5120 -> 512, 3% mismatches, tiles against mismatch rows: 768 slots, 15360
-//    stages, V=16000 31.5 and 33.0 us; 896 slots V=16000 37.2 and 32.6, V=32000 44.4 and 43.0,
-//    V=128256 93.2 and 100.6; 1024 slots V=64000 73.7 and 69.8, V=128256 105.9 and 113.7; 16
-//    trees of 60 nodes, V=128256 93.2 and 90.3).
+//  - Not where the tiles are the most and the longest and the reduction too short to hide them: with
+//    the whole device they take about 0.95 ns a stage.  Few mismatches then cost less after the
+//    reduction (5120 -> 512, 3% mismatches, tiles against mismatch rows: 1024 slots, 20480 stages,
+//    V=64000 71.8 and 69.2 us, V=128256 104.4 and 113.6; 16 trees of 60 nodes, 19200 stages,
+//    V=128256 93.0 and 89.9; 896 slots, 17920 stages, V=16000 30.7 and 32.5, V=64000 60.0 and
+//    62.7).
 int32_t head_tile_groups(int64_t m_cap, const cospec_head *hd, int64_t logit_bytes) {
     constexpr int64_t kCus = 256, kMostHidden = 12 << 20;
     if (hd->dtype != COSPEC_BF16 || m_cap < kTilesMinSlots) return 0;
@@ -126,10 +128,10 @@ int32_t head_tile_groups(int64_t m_cap, const cospec_head *hd, int64_t logit_byt
     if (2 * tiles > kCus || m_cap * hd->d * 2 > kMostHidden || ksplit_for(m_cap, hd) < kHeadTileGroups) return 0;
     const double reduce_us = static_cast<double>(logit_bytes) / 6.5e6, tile_us = hd->d / 32 * 0.8;
     const int64_t stages = tiles * (hd->d / 32);
-    if (stages > 16000 && reduce_us < 4 * 0.95e-3 * stages) return 0;
+    if (stages > 18500 && reduce_us < 4 * 0.95e-3 * stages) return 0;
     int32_t groups = kHeadTileGroups;
     while (tiles * groups > kCus) groups /= 2;
-    while (groups < kHeadTileGroups && tile_us > groups * reduce_us) groups *= 2;
+    while (groups < kHeadTileGroups && tiles * groups <= kCus && tile_us > groups * reduce_us) groups *= 2;
     return groups;
 }
 

@@ -12,7 +12,7 @@
 // MFMAs) accumulates a 64 x 32 sub-tile (4 x 2 MFMA tiles).  The slice's
 // partial U goes to the workspace.
 //
-// k_head_gemm (trees): one workgroup per (tile, slice) of the list's capacity;
+// k_head_gemm (trees, cospec_arbitrate): one workgroup per (tile, slice) of the list's capacity;
 // M (the number of mismatches) is read on the device, workgroups past it exit.
 // k_head_gemm_loop (chains): one workgroup per resident slot; each derives M
 // and the list itself (or reads them) and loops over the items of the M rows

@@ -322,9 +322,8 @@ def test_static_scratch_entry_point_rejects_before_any_launch():
     (0, 64, 7, 151936, 4096, 256, 8),      # 28 tiles
     (0, 48, 25, 128256, 4096, 256, 2),     # 76 tiles: two groups stay at one workgroup per CU
     (0, 128, 7, 151936, 5120, 512, 2),     # 112 long tiles behind 90 us of reduction
-    (0, 128, 7, 16000, 5120, 512, 0),      # ... and behind 9 us: they would outlast it
-    (0, 256, 4, 64000, 5120, 512, 0), (0, 256, 4, 128256, 5120, 512, 2),
-    (0, 96, 8, 16000, 5120, 512, 8),       # 96 tiles are short enough anywhere
+    (0, 128, 7, 16000, 5120, 512, 4),      # ... and behind 9 us: shorter, at two workgroups per CU
+    (0, 256, 4, 64000, 5120, 512, 0), (0, 256, 4, 128256, 5120, 512, 2),     # 128 of them outlast 45 us
     (1, 16, 60, 128256, 5120, 512, 0), (1, 12, 60, 128256, 5120, 512, 4),
     (0, 6, 8, 32000, 4096, 256, 0), (0, 7, 7, 32000, 4096, 256, 8),          # 48 and 49 slots
     (0, 7, 7, 32000, 448, 256, 0), (0, 7, 7, 32000, 456, 256, 8),            # seven and eight stages of d

@@ -1136,19 +1136,18 @@ def _phases_case(B, K, V, d, h, ldt, packed, t1, groups):
     parity.check_block(gpu, _ref_block(wl, 0.4, u, cand))
 
 
-# A short vocabulary leaves the tiles nothing to hide behind: eight workgroups share each
-@pytest.mark.parametrize("B,K,d,h,ldt,packed,t1", [
-    (7, 7, 512, 65, "bf16", False, False),      # 49 slots, one column past a tile, slices of one piece
-    (16, 4, 520, 64, "bf16", True, False),      # one whole tile; d past five slices of 96, two empty
-    (13, 5, 456, 128, "f32", False, False),     # 65 slots, slices of 64 and a last one of eight elements, fp32 logits
-    (41, 25, 1024, 256, "bf16", False, True),   # 17 x 4 tiles, temperature 1
-    (40, 12, 640, 600, "bf16", True, True),     # 8 x 10 tiles, h past whole tiles
-    (60, 17, 512, 512, "bf16", False, False),   # 16 x 8 = 128 tiles, the most
-    (61, 17, 512, 512, "bf16", False, False),   # 17 x 8: past them, on the mismatch rows
+@pytest.mark.parametrize("B,K,d,h,ldt,packed,t1,groups", [
+    (7, 7, 512, 65, "bf16", False, False, 8),      # 49 slots, one column past a tile, slices of one piece
+    (16, 4, 520, 64, "bf16", True, False, 8),      # one whole tile; d past five slices of 96, two empty
+    (13, 5, 456, 128, "f32", False, False, 8),     # 65 slots, slices of 64 and a last one of eight elements, fp32 logits
+    (41, 25, 1024, 256, "bf16", False, True, 4),   # 17 x 4 tiles, temperature 1
+    (40, 12, 640, 600, "bf16", True, True, 4),     # 8 x 10 tiles, h past whole tiles
+    (60, 17, 512, 512, "bf16", False, False, 4),   # 16 x 8 = 128 tiles, the most
+    (61, 17, 512, 512, "bf16", False, False, 0),   # 17 x 8: past them, on the mismatch rows
 ])
-def test_chain_head_tiles(B, K, d, h, ldt, packed, t1):
+def test_chain_head_tiles(B, K, d, h, ldt, packed, t1, groups):
     # the head's first layer in 64 x 64 tiles over every decision slot
-    _phases_case(B, K, 3001, d, h, ldt, packed, t1, 0 if B == 61 else 8)
+    _phases_case(B, K, 3001, d, h, ldt, packed, t1, groups)
 
 
 @pytest.mark.parametrize("B,K,V,d,h,packed,t1,groups", [
