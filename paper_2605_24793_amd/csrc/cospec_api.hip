@@ -455,8 +455,9 @@ cospec_status run(const Common &c, Phase phase, int32_t *accept_len, int32_t *ou
         }
 
         if (!record(c.opts ? c.opts->reduce_begin : nullptr)) return COSPEC_ERR_HIP;
-        const hipError_t re = tiles ? launch_reduce_tiles(dt, ra, ha, c.stream) : every_slot ? launch_reduce_head(dt, static_cast<Dtype>(c.head->dtype), ra, ha, c.stream)
-                                         : launch_reduce(dt, ra, c.stream);
+        const hipError_t re = tiles        ? launch_reduce_tiles(dt, ra, ha, c.stream)
+                              : every_slot ? launch_reduce_head(dt, static_cast<Dtype>(c.head->dtype), ra, ha, c.stream)
+                                           : launch_reduce(dt, ra, c.stream);
         if (re != hipSuccess) return COSPEC_ERR_HIP;
         if (!record(c.opts ? c.opts->reduce_end : nullptr)) return COSPEC_ERR_HIP;
         // the second pair brackets nothing: back to back, it measures what an event

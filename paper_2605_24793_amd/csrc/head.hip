@@ -634,7 +634,7 @@ int32_t head_ksplit(int64_t m_cap, int32_t d, int32_t h, int32_t elem_bytes) {
 int32_t head_alone_group(int64_t n_sel, int64_t n_rows, int32_t d, int32_t h, int32_t elem_bytes) {
     const int64_t tiles = (n_sel + kHeadTileM - 1) / kHeadTileM * ((h + kHeadTileN - 1) / kHeadTileN);
     const int64_t ks = head_ksplit(n_sel, d, h, elem_bytes), row = static_cast<int64_t>(d) * elem_bytes;
-    if (elem_bytes != 2 || n_rows * row > kRawMax || h * row > kRawMax) return 1;   // raw buffers: 32-bit offsets
+    if (elem_bytes != 2 || n_rows > kRawMax / row || h > kRawMax / row) return 1;   // raw buffers: 32-bit offsets
     int64_t per = 1;
     while (per < ks && tiles * ((ks + per - 1) / per) > kHeadMostBlocks) per *= 2;
     return static_cast<int32_t>(std::min(per, ks));

@@ -18,7 +18,7 @@
 // one the second layer adds them in the same groups (HeadArgs::zgroup).  So z is the same bits
 // in both forms.  The slices are as many as the tiled GEMM and the slot GEMM take at the same
 // sizes (8, 16 or 32): with 8 throughout, the relative error of z grew where those take more
-// (120 slots, 4096 -> 256: 1.0e-7 -> 1.4e-7).  Workgroups of one slice group stay on the same
+// (120 slots, 4096 -> 256: 1.48e-7 -> 1.73e-7, now 1.36e-7).  Workgroups of one slice group stay on the same
 // XCDs (the groups, 2, 4 or 8 of them, are dealt with the workgroups), whose L2 then reads
 // that part of the operands.
 #pragma once
