@@ -198,9 +198,9 @@ int32_t cu_count() {
 //    slots, one split 85.6% of the HBM peak, two 84.9%, three 83.8%);
 //  - fewer rows: about four rounds of pieces, so that every slot stays busy and the
 //    last round is short (the peaked chain batch, 960 rows: one split 82%, nine 86%),
-//    but at least four vectors per lane, so every lane keeps its loads in flight (the
-//    small chain batch's reduction 4.8 us at 15 splits against 9.9 us at 62; the tiny
-//    chain's 1.2 against 2.4 us at 8 and 4 splits).
+//    but at least four vectors per lane, so every lane keeps its loads in flight (on one
+//    input set, which stays in the caches: the small chain batch's reduction 4.8 us at 15
+//    splits against 9.9 us at 62; the tiny chain's 1.2 against 2.4 us at 8 and 4 splits).
 int32_t auto_splits(int64_t rows, int64_t nvec, int64_t slots) {
     if (rows <= 0) return 1;
     if (2 * rows >= 3 * slots) return 1;
