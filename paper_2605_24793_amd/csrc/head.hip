@@ -493,7 +493,7 @@ __device__ inline void gemm_tile(const HeadArgs &a, int64_t M, int64_t m_base, i
 // SUMS (cospec_arbitrate): a workgroup takes a.kgroup consecutive slices.  Its second set of sums
 // costs 32 registers; raw buffers in place of pointers leave it two workgroups per CU.
 template <int DT, int kRing, bool SUMS>
-__global__ __launch_bounds__(64 * kGemmWaves) __attribute__((amdgpu_waves_per_eu(kRing == kRingShallow ? 4 : 2)))
+__global__ __launch_bounds__(64 * kGemmWaves) __attribute__((amdgpu_waves_per_eu(SUMS ? 4 : 2)))
 void k_head_gemm(HeadArgs a) {
     constexpr int BK = kStageBytes / (DT == kBF16 ? 2 : 4);
     __shared__ __attribute__((aligned(16))) char ring[kRing][2 * kHeadTileM * kStageBytes];
@@ -581,18 +581,17 @@ __global__ __launch_bounds__(kReduceThreads) void k_tile_gemm(HeadArgs a) {
     tilegemm::run<tilegemm::kAlone>(a, blockIdx.x, s_ring, reinterpret_cast<const u32x4 *>(kZeroVec));
 }
 
-// z[m] = w2 . relu(sum_ks upart[ks][m] + b1) + b2 of list entry m (out_by_slot: its partials
-// are at its decision slot, the entry itself), one wave per row, fixed order.  ARB
-// (cospec_arbitrate): z goes to the caller with its threshold decision; an index outside
-// [0, n_rows) has z = NaN and accept 0.
-template <int DT, bool ARB>
+// z[m] = w2 . relu(sum_ks upart[ks][m] + b1) + b2 of list entry m (SLOT: its partials are at
+// its decision slot, the entry itself; only then do their loads wait for the list's), one wave
+// per row, fixed order.  ARB (cospec_arbitrate): z goes to the caller with its threshold
+// decision; an index outside [0, n_rows) has z = NaN and accept 0.
+template <int DT, bool ARB, bool SLOT>
 __global__ __launch_bounds__(256) void k_head_epilogue(HeadArgs a, ArbOut o) {
     const int64_t M = a.count_dev ? static_cast<int64_t>(*a.count_dev) : a.count_host;
     const int64_t m = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (m >= M) return;
     const int64_t e = a.list ? static_cast<int64_t>(a.list[m]) : m;
-    // (cospec_arbitrate's rows are list positions: their loads need not wait for the list's)
-    const float z = headz::head_z<DT, headz::kFew>(a, !ARB && a.out_by_slot ? e : m, e, threadIdx.x & 63, a.ksplit);
+    const float z = headz::head_z<DT, headz::kFew>(a, SLOT ? e : m, e, threadIdx.x & 63, a.ksplit);
     if ((threadIdx.x & 63) != 0) return;
     if constexpr (ARB) {
         if (o.z) o.z[m] = z;
@@ -733,11 +732,13 @@ hipError_t launch_head_epilogue(Dtype dt, const HeadArgs &a, const ArbOut *out, 
     if (egrid.x == 0) return hipSuccess;
     const ArbOut o = out ? *out : ArbOut{};
     if (dt == kBF16) {
-        if (out) hipLaunchKernelGGL((k_head_epilogue<kBF16, true>), egrid, block, 0, s, a, o);
-        else hipLaunchKernelGGL((k_head_epilogue<kBF16, false>), egrid, block, 0, s, a, o);
+        if (out) hipLaunchKernelGGL((k_head_epilogue<kBF16, true, false>), egrid, block, 0, s, a, o);
+        else if (a.out_by_slot) hipLaunchKernelGGL((k_head_epilogue<kBF16, false, true>), egrid, block, 0, s, a, o);
+        else hipLaunchKernelGGL((k_head_epilogue<kBF16, false, false>), egrid, block, 0, s, a, o);
     } else {
-        if (out) hipLaunchKernelGGL((k_head_epilogue<kF32, true>), egrid, block, 0, s, a, o);
-        else hipLaunchKernelGGL((k_head_epilogue<kF32, false>), egrid, block, 0, s, a, o);
+        if (!out && a.out_by_slot) return hipErrorInvalidValue;         // bf16 heads only
+        if (out) hipLaunchKernelGGL((k_head_epilogue<kF32, true, false>), egrid, block, 0, s, a, o);
+        else hipLaunchKernelGGL((k_head_epilogue<kF32, false, false>), egrid, block, 0, s, a, o);
     }
     return hipGetLastError();
 }
